@@ -49,17 +49,71 @@ struct RtArgs {
   int32_t dirfd;
 };
 
-// The work-group copies n bytes from HBM to host staging: 16-byte vectors
-// when both ends are 16-byte aligned, then the remaining bytes one by one.
-__device__ __forceinline__ void copy_to_host(uint64_t dst, const uint8_t* src, uint64_t n) {
-  uint64_t head = 0;
-  if (((dst | (uint64_t)src) & 15) == 0) {
-    const uint64_t nv = n / 16;
-    for (uint64_t i = threadIdx.x; i < nv; i += blockDim.x)
-      stg16(dst + 16 * i, ldg16((uint64_t)src + 16 * i));
-    head = nv * 16;
+// Copies and compares between host staging and HBM.  The host side of every
+// 16-byte vector is aligned (the bytes before the first such address and after
+// the last are done one by one); the HBM side may lie at any byte address, as
+// pieces of odd length do (a global load needs no alignment).  Each work-item
+// keeps kDeep vectors in flight: the staging side is a host-link round trip of
+// about 2 us, so what one work-group moves is bound by the bytes it keeps in
+// flight (256 work-items x 8 x 16 B = 32 KiB), not by the link.  With one
+// byte per work-item, the round trip of 64 files x 4 MiB in 1 MiB pieces took
+// 34.8 ms, most of it in the compare; with these and the compare overlapped
+// with the reads it takes 15.0 ms, bound by the host's write() and read().
+constexpr uint32_t kDeep = 8;
+typedef u32x4 u32x4_u __attribute__((aligned(1)));
+__device__ __forceinline__ u32x4 ldg16_any(const uint8_t* p) { return *gp<const u32x4_u>((uint64_t)p); }
+
+// Bytes of [0, n) before the first 16-byte boundary at or after `a`.
+__device__ __forceinline__ uint64_t head_bytes(uint64_t a, uint64_t n) {
+  return min<uint64_t>(n, (0 - a) & 15);
+}
+
+// Work-items 0 .. nt - 1 copy n bytes from HBM to host staging.
+__device__ void copy_to_host(uint64_t dst, const uint8_t* src, uint64_t n, uint32_t t,
+                             uint32_t nt) {
+  const uint64_t h = head_bytes(dst, n), nv = (n - h) / 16, tail = h + nv * 16;
+  if (t < h) gp<uint8_t>(dst)[t] = gp(src)[t];
+  uint64_t i = t;
+  for (; i + (kDeep - 1) * (uint64_t)nt < nv; i += kDeep * (uint64_t)nt) {
+    u32x4 v[kDeep];
+#pragma unroll
+    for (uint32_t k = 0; k < kDeep; ++k) v[k] = ldg16_any(src + h + 16 * (i + k * (uint64_t)nt));
+#pragma unroll
+    for (uint32_t k = 0; k < kDeep; ++k) stg16(dst + h + 16 * (i + k * (uint64_t)nt), v[k]);
   }
-  for (uint64_t i = head + threadIdx.x; i < n; i += blockDim.x) gp<uint8_t>(dst)[i] = src[i];
+  for (; i < nv; i += nt) stg16(dst + h + 16 * i, ldg16_any(src + h + 16 * i));
+  if (tail + t < n) gp<uint8_t>(dst)[tail + t] = gp(src)[tail + t];
+}
+
+// Bytes of x that are not zero.
+__device__ __forceinline__ uint32_t nonzero_bytes(u32x4 x) {
+  uint32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    c += __popc((((x[i] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x[i]) & 0x80808080u);
+  return c;
+}
+
+// This work-item's count of the bytes of [0, n) that differ between host
+// staging and HBM (work-items 0 .. nt - 1 share the range).
+__device__ uint32_t count_diff(uint64_t back, const uint8_t* src, uint64_t n, uint32_t t,
+                               uint32_t nt) {
+  const uint64_t h = head_bytes(back, n), nv = (n - h) / 16, tail = h + nv * 16;
+  uint32_t bad = 0;
+  if (t < h) bad += gp<const uint8_t>(back)[t] != gp(src)[t];
+  uint64_t i = t;
+  for (; i + (kDeep - 1) * (uint64_t)nt < nv; i += kDeep * (uint64_t)nt) {
+    u32x4 v[kDeep], w[kDeep];
+#pragma unroll
+    for (uint32_t k = 0; k < kDeep; ++k) v[k] = ldg16(back + h + 16 * (i + k * (uint64_t)nt));
+#pragma unroll
+    for (uint32_t k = 0; k < kDeep; ++k) w[k] = ldg16_any(src + h + 16 * (i + k * (uint64_t)nt));
+#pragma unroll
+    for (uint32_t k = 0; k < kDeep; ++k) bad += nonzero_bytes(v[k] ^ w[k]);
+  }
+  for (; i < nv; i += nt) bad += nonzero_bytes(ldg16(back + h + 16 * i) ^ ldg16_any(src + h + 16 * i));
+  if (tail + t < n) bad += gp<const uint8_t>(back)[tail + t] != gp(src)[tail + t];
+  return bad;
 }
 
 template <O o>
@@ -90,7 +144,7 @@ __global__ __launch_bounds__(kWG) void roundtrip(RtArgs A) {
   if (wfd < 0) return;
   for (uint32_t p = 0; p < A.pieces; ++p) {
     const uint32_t n = piece_len(p);
-    copy_to_host(wst + (uint64_t)p * A.piece, src + (uint64_t)p * A.piece, n);
+    copy_to_host(wst + (uint64_t)p * A.piece, src + (uint64_t)p * A.piece, n, threadIdx.x, kWG);
     // a producer: the call's barrier before makes every work-item's stores
     // visible to the host first
     const int64_t r = call_wg<o, B::Blocking>(
@@ -107,19 +161,28 @@ __global__ __launch_bounds__(kWG) void roundtrip(RtArgs A) {
       Args6{{(uint64_t)(int64_t)A.dirfd, path, (uint64_t)O_RDONLY, 0, 0, 0}});
   put(rfd);
   if (rfd < 0) return;
-  for (uint32_t p = 0; p < A.pieces; ++p)
+  // The reads are consumers: the barrier after each one orders the loads of
+  // its piece after the host's data.  A consumer call has no barrier before
+  // it, so the caller's wavefront issues the next read at once and the others
+  // compare the piece that has just arrived while the host serves that read
+  // (into another piece's bytes; the read at the end of the file stores
+  // nothing).  A piece is final when its own read has returned.
+  uint32_t bad = 0;
+  auto compare = [&](uint32_t p) {
+    if (threadIdx.x >= 64)
+      bad += count_diff(rst + (uint64_t)p * A.piece, src + (uint64_t)p * A.piece, piece_len(p),
+                        threadIdx.x - 64, kWG - 64);
+  };
+  for (uint32_t p = 0; p < A.pieces; ++p) {
+    if (p) compare(p - 1);
     put(call_wg<O::Relaxed, B::Blocking>(
         A.c, GSYS_NR_READ, 0,
         Args6{{(uint64_t)rfd, rst + (uint64_t)p * A.piece, piece_len(p), 0, 0, 0}}));
+  }
+  if (A.pieces) compare(A.pieces - 1);
   put(call_wg<O::Relaxed, B::Blocking>(A.c, GSYS_NR_READ, 0,
                                        Args6{{(uint64_t)rfd, rst, kEofRead, 0, 0, 0}}));
   put(call_wg<O::Relaxed, B::Blocking>(A.c, GSYS_NR_CLOSE, 0, Args6{{(uint64_t)rfd, 0, 0, 0, 0, 0}}));
-
-  // the reads were consumers: their barrier after orders the loads below
-  // after the host's data; the end-of-file read stored nothing
-  uint32_t bad = 0;
-  const gptr_t<const uint8_t> back = gp<const uint8_t>(rst);
-  for (uint64_t i = threadIdx.x; i < A.file_bytes; i += blockDim.x) bad += back[i] != src[i];
   if (bad) atomicAdd(&A.mismatch[f], (unsigned long long)bad);
 }
 
@@ -145,7 +208,7 @@ __device__ __forceinline__ void slice(uint64_t bytes, uint64_t* lo, uint64_t* hi
 __global__ __launch_bounds__(kWG) void kernel_write(KioArgs A) {
   uint64_t lo, hi;
   slice(A.bytes, &lo, &hi);
-  copy_to_host(A.staging + lo, A.data + lo, hi - lo);
+  copy_to_host(A.staging + lo, A.data + lo, hi - lo, threadIdx.x, kWG);
   const int64_t r = call_kernel<B::Blocking>(
       A.c, A.ks, GSYS_NR_WRITE, 0, [] {},
       [&] { return Args6{{(uint64_t)(int64_t)A.fd, A.staging, A.bytes, 0, 0, 0}}; });
@@ -163,9 +226,7 @@ __global__ __launch_bounds__(kWG) void kernel_read(KioArgs A) {
   if (r < 0) return;
   uint64_t lo, hi;
   slice(min<uint64_t>(A.bytes, (uint64_t)r), &lo, &hi);
-  const gptr_t<const uint8_t> back = gp<const uint8_t>(A.staging);
-  uint32_t bad = 0;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) bad += back[i] != A.data[i];
+  const uint32_t bad = count_diff(A.staging + lo, A.data + lo, hi - lo, threadIdx.x, kWG);
   if (bad) atomicAdd(&A.mismatch[0], (unsigned long long)bad);
 }
 

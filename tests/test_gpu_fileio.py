@@ -134,3 +134,29 @@ def test_kernel_granularity_append_then_consume(gs, tmpdata, grid):
     finally:
         ctx.allow_fd(rfd, 0)
         os.close(rfd)
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 4096 * 8 + 31, (1 << 20) + 3])
+@pytest.mark.parametrize("grid", [1, 3, 61])
+def test_compare_counts_every_differing_byte(gs, tmpdata, n, grid):
+    """The 16-byte compare counts exactly the bytes that differ: slices and
+    data at odd addresses, differences at both ends, around vector edges and
+    several in one vector."""
+    g, ctx = gs
+    from paper_1705_06965_amd.fileio import kernel_io
+    rng = np.random.default_rng([n, grid])
+    part = rng.integers(0, 256, n, dtype=np.uint8)
+    at = np.unique(np.concatenate([[0, n - 1], np.arange(14, 19), rng.integers(0, n, 60)]).clip(0, n - 1))
+    want = part.copy()
+    want[at] ^= rng.integers(1, 256, len(at)).astype(np.uint8)
+    p = os.path.join(tmpdata, "cmp.bin")
+    part.tofile(p)
+    rfd = os.open(p, os.O_RDONLY)
+    ctx.allow_fd(rfd, g.FD_READ)
+    say("compare", n, grid)
+    try:
+        ret, mism = kernel_io(ctx, rfd, g.NR_READ, want, grid=grid)
+        assert ret == n and mism == len(at)
+    finally:
+        ctx.allow_fd(rfd, 0)
+        os.close(rfd)
