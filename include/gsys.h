@@ -306,7 +306,9 @@ const char *gsys_strerror(int code);
  *             GSYS_PERSISTENT_GRID sets it instead): every work-group waiting
  *             for its call polls host memory, which slows the host pool, and
  *             64 groups of 256 keep enough reads in flight.
- *   wg_size   work-items per work-group: 64, 128, 256, 512 or 1024
+ *   wg_size   work-items per work-group: 64, 128, 256, 512 or 1024.  A launch
+ *             may give its work-groups further wavefronts that make no calls
+ *             and help to hash (items of more than 512 bytes).
  * item_bytes must be a multiple of 64 and at most 1 MiB; n_items % wg_size
  * need not be 0 (the tail work-group is partial).  n_items == 0 returns 0 at
  * once, launching nothing.
@@ -669,8 +671,9 @@ int gsys_file_kernel_io(gsys_ctx *ctx, int fd, uint32_t nr, uint64_t data, uint6
  * host has already read every item into `staging` (any device-readable
  * address: registered host memory or HBM); one kernel computes
  * out_fnv[i] = FNV-1a-64 of the first rets[i] bytes (rets: device int64[n],
- * values <= 0 hash nothing) of staging + i * item_bytes.  grid 0 = one
- * work-group per wg_size items, otherwise a grid-stride loop over them.
+ * values <= 0 hash nothing) of staging + i * item_bytes.  grid 0 = as many
+ * work-groups as the items fill, otherwise a grid-stride loop of `grid`
+ * work-groups of wg_size work-items over them.
  * n_items == 0 returns 0 at once (the pointers may then be null).
  * Errors: -EINVAL.
  */

@@ -618,6 +618,8 @@ uint32_t resident_grid(gsys_ctx* c, const void* kernel, uint32_t block, uint32_t
 
 uint32_t persistent_grid_override(gsys_ctx* c) { return c->grid_override; }
 
+uint32_t cu_count(gsys_ctx* c) { return (uint32_t)c->cu_count; }
+
 uint64_t ticks_per_ms(gsys_ctx* c) { return c->wall_khz; }
 
 int control_page(gsys_ctx* c, void** host, uint64_t* dev) {

@@ -1,5 +1,6 @@
-// FNV-1a-64 of many items at once on gfx950: one lane per item (the hash is
-// a serial byte chain), items staged through LDS with coalesced loads.
+// FNV-1a-64 of many items at once on gfx950, staged through LDS with coalesced
+// loads: one lane per item running the serial byte chain (wave_fnv_t), or many
+// lanes per item (wave_fnv_par).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -120,6 +121,416 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
     __builtin_amdgcn_wave_barrier();
   }
   return h;
+}
+
+// ---------------------------------------------------------------------------
+// FNV-1a-64 of one item by many lanes.
+//
+// h' = (h ^ b) * p is serial, but its parts are not.  Let s be the low byte of
+// h and x = s ^ b; the XOR adds x - s to h, so
+//   h_n = p^n h_0 + sum_i (x_i - s_i) p^(n - i)   (mod 2^64),
+// a plain weighted sum once the low bytes are known, and those follow their
+// own recurrence s' = 179 x mod 256 (179 = p mod 256).  Bit j of 179 x is bit
+// j of x XOR a function of x's lower bits, so with the bits below j known at
+// every position, bit j of all the s is a running XOR along the item: eight
+// running XORs, one per bit, each a parallel prefix.
+//
+// A lane holds 128 consecutive bytes, four to a 32-bit word and 32 words, as
+// eight bit planes of four words: bit w of plane word t is the bit of byte
+// 4 w + t.  A plane's running XOR takes three XORs down the four words, a
+// five-step prefix in one word and one ballot across the lanes.  The weighted
+// sum goes to the matrix cores: int8 MFMAs of the x (and of the s, subtracted)
+// with the eight balanced base-256 digits of the powers of p; one column sums
+// 512 bytes.  Bytes past an item's end are zeros: a zero byte multiplies h by
+// p, which the inverse of p undoes.
+//
+// Bound by vector-ALU issue: 821 instructions and 16 MFMAs per 8 KiB step of
+// a wavefront (27 cycles per byte and lane; the serial chain takes 32), but a
+// 4 KiB item takes half a step instead of the chain's 61 us.  Measured: 50,000
+// items of 4 KiB in HBM 110 -> 61 us (3.4 TB/s), 180 of 1 MiB 15.4 -> 0.27 ms,
+// 64 of 4 KiB read and hashed by one work-group 99 -> 38 us.
+
+constexpr uint64_t kFnvPrime = 0x100000001b3ull;
+constexpr uint64_t kFnvBasis = 0xcbf29ce484222325ull;
+constexpr uint32_t kSegBytes = 128;               // per lane and step
+constexpr uint32_t kStepBytes = 64 * kSegBytes;   // per wavefront and step
+constexpr uint32_t kColBytes = 4 * kSegBytes;     // summed by one MFMA column
+constexpr uint32_t kSegStride = kSegBytes + 16;   // in LDS: conflict-free 16-byte reads
+// Wave tile: the step's bytes, then the byte counts of two groups of items.
+constexpr uint32_t kParTile = 64 * kSegStride + 2 * 16 * 4;
+// Items up to this size are hashed one per lane (wave_fnv_t): a matrix column
+// sums 512 bytes of one item, so a shorter one would waste lanes, and its
+// chain is short (8 us for 512 bytes).
+constexpr uint32_t kParMinItem = 512;
+
+struct FnvWeights {
+  // [t * 2 + half][lane][register]: four digits of one plane per register
+  uint32_t a[8][64][4];
+  uint64_t col[16];    // p^(512 k)
+  uint64_t seg[8];     // p^(128 * 2^k)
+  uint64_t inv[24];    // p^-(2^k)
+};
+constexpr FnvWeights fnv_weights() {
+  FnvWeights w{};
+  uint64_t pw[kColBytes + 1] = {};
+  pw[0] = 1;
+  for (uint32_t i = 1; i <= kColBytes; ++i) pw[i] = pw[i - 1] * kFnvPrime;
+  uint8_t digit[kColBytes + 1][8] = {};
+  for (uint32_t i = 0; i <= kColBytes; ++i) {
+    uint64_t r = pw[i];
+    for (uint32_t m = 0; m < 8; ++m) {
+      digit[i][m] = (uint8_t)r;
+      r = (r >> 8) + ((r >> 7) & 1u);  // digits 128..255 stand for -128..-1
+    }
+  }
+  for (uint32_t op = 0; op < 8; ++op)
+    for (uint32_t lane = 0; lane < 64; ++lane)
+      for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t m = lane & 15, g = lane >> 4, t = op >> 1, half = op & 1;
+        uint32_t v = 0;
+        if (m < 8)
+          for (uint32_t c = 0; c < 4; ++c) {
+            const uint32_t o = g * kSegBytes + 4 * (8 * c + 4 * half + q) + t;
+            v |= (uint32_t)digit[kColBytes - o][m] << (8 * c);
+          }
+        w.a[op][lane][q] = v;
+      }
+  w.col[0] = 1;
+  for (uint32_t k = 1; k < 16; ++k) w.col[k] = w.col[k - 1] * pw[kColBytes];
+  w.seg[0] = pw[kSegBytes];
+  for (uint32_t k = 1; k < 8; ++k) w.seg[k] = w.seg[k - 1] * w.seg[k - 1];
+  uint64_t iv = kFnvPrime;  // Newton: p * iv = 1 mod 2^64
+  for (int k = 0; k < 6; ++k) iv *= 2 - kFnvPrime * iv;
+  w.inv[0] = iv;
+  for (uint32_t k = 1; k < 24; ++k) w.inv[k] = w.inv[k - 1] * w.inv[k - 1];
+  return w;
+}
+static __device__ const FnvWeights fnv_w = fnv_weights();
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void opaque(uint32_t& v) { asm("" : "+v"(v)); }
+
+// Three-input operations, one instruction each (the compiler does not find
+// all of them by itself).  bfi: a where m is set, b elsewhere.
+__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_bitop3_b32(m, a, b, 0xca);
+}
+
+// 8 x 8 bit transpose in every byte column: bit j of byte c of a[r] <-> bit r
+// of byte c of a[j].
+__device__ __forceinline__ void transpose_bits(uint32_t (&a)[8]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t s = 1u << k, m = k == 0 ? 0x55555555u : k == 1 ? 0x33333333u : 0x0f0f0f0fu;
+#pragma unroll
+    for (uint32_t r = 0; r < 8; ++r)
+      if (!(r & s)) {
+        const uint32_t lo = a[r], hi = a[r + s];
+        a[r] = bfi(m, lo, hi << s);
+        a[r + s] = bfi(m, lo >> s, hi);
+      }
+  }
+}
+
+__device__ __forceinline__ uint32_t maj(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0xe8);
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+template <int ctrl>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctrl, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), ctrl, 0xf, 0xf, true);
+  return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
+  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
+  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Lanes an item occupies in a step (a power of two of at least one column, at
+// most the wavefront) as a shift.
+__host__ __device__ inline uint32_t par_lanes_log2(uint32_t item_bytes) {
+  uint32_t k = 2;
+  while (k < 6 && (kSegBytes << k) < item_bytes) ++k;
+  return k;
+}
+
+// The items a wavefront takes at once.
+__host__ __device__ inline uint32_t par_items(uint32_t item_bytes) {
+  return 64u >> par_lanes_log2(item_bytes);
+}
+
+// The sum of the item's (x - s) p^(bytes to the end of its slot of 128 << ll
+// bytes in this step), in every lane of the item.  w: the lane's 128 bytes;
+// ent: low byte of the item's hash before the step; before: lanes holding
+// earlier bytes of the same item; wt(k): the weights' operand k.
+template <class Weights>
+__device__ __forceinline__ uint64_t par_step(uint32_t (&w)[32], uint32_t ent, uint64_t before,
+                                             Weights wt, uint64_t colw, uint32_t ll) {
+  // bytes to (t, r): byte c of b[t][r] is byte t of word 8 c + r
+  uint32_t b[4][8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const uint32_t p0 = __builtin_amdgcn_perm(w[8 + r], w[r], 0x05010400u);
+    const uint32_t p1 = __builtin_amdgcn_perm(w[8 + r], w[r], 0x07030602u);
+    const uint32_t p2 = __builtin_amdgcn_perm(w[24 + r], w[16 + r], 0x05010400u);
+    const uint32_t p3 = __builtin_amdgcn_perm(w[24 + r], w[16 + r], 0x07030602u);
+    b[0][r] = __builtin_amdgcn_perm(p2, p0, 0x05040100u);
+    b[1][r] = __builtin_amdgcn_perm(p2, p0, 0x07060302u);
+    b[2][r] = __builtin_amdgcn_perm(p3, p1, 0x05040100u);
+    b[3][r] = __builtin_amdgcn_perm(p3, p1, 0x07060302u);
+  }
+  // The scheduling barriers and opaque values keep one stage's temporaries
+  // from overlapping the next one's: without them the compiler regroups the
+  // XORs and interleaves the stages until the registers spill.
+  uint32_t x[4][8];  // planes of b, then of x
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      opaque(b[t][r]);
+      x[t][r] = b[t][r];
+    }
+    transpose_bits(x[t]);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) opaque(x[t][r]);
+  }
+  // 179 x = y + 16 y + 128 x with y = x + 2 x: carries cy of the first sum, cz
+  // of the second
+  uint32_t y[4][8], cy[4], cz[4];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t gj[4], v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (j == 0) gj[t] = 0;
+      if (j == 1) gj[t] = x[t][0];
+      if (j == 2 || j == 3) gj[t] = x[t][j - 1] ^ cy[t];
+      if (j >= 4) gj[t] = xor3(x[t][j - 1], cy[t], y[t][j - 4]);
+      if (j == 5 || j == 6) gj[t] ^= cz[t];
+      if (j == 7) gj[t] = xor3(gj[t], cz[t], x[t][0]);
+      v[t] = j == 0 ? (t ? x[t][j] ^ v[t - 1] : x[t][j])
+                    : t ? xor3(x[t][j], gj[t], v[t - 1]) : x[t][j] ^ gj[t];
+    }
+    uint32_t run = v[3];
+    run ^= run << 1;
+    run ^= run << 2;
+    run ^= run << 4;
+    run ^= run << 8;
+    run ^= run << 16;
+    const uint64_t odd = __ballot((int32_t)run < 0) & before;
+    const uint32_t par = (uint32_t)__popcll(odd) ^ (ent >> j);
+    const uint32_t in = xor3(run, v[3], 0u - (par & 1u));  // bit j of s before word w
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[t][j] = j == 0 ? v[t] ^ in : xor3(v[t], in, gj[t]);
+      if (j == 0) y[t][0] = x[t][0];
+      if (j == 1) y[t][1] = x[t][1] ^ x[t][0];
+      if (j >= 2 && j < 7) y[t][j] = xor3(x[t][j], x[t][j - 1], cy[t]);
+      if (j >= 4 && j < 7)
+        cz[t] = j >= 5 ? maj(y[t][j], y[t][j - 4], cz[t]) : y[t][j] & y[t][j - 4];
+      if (j >= 1 && j < 7)
+        cy[t] = j >= 2 ? maj(x[t][j], x[t][j - 1], cy[t]) : x[t][j] & x[t][j - 1];
+      opaque(x[t][j]);
+      if (j < 4) opaque(y[t][j]);
+      if (j >= 1 && j < 7) opaque(cy[t]);
+      if (j >= 4 && j < 7) opaque(cz[t]);
+    }
+  }
+  // back to bytes, as signed numbers 128 lower (the sums cancel the offset)
+  i32x4 dx = {0, 0, 0, 0}, ds = {0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    __builtin_amdgcn_sched_barrier(0);
+    x[t][7] = ~x[t][7];
+    transpose_bits(x[t]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      i32x4 bx, bs;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        bx[q] = (int)x[t][4 * h + q];
+        bs[q] = (int)(x[t][4 * h + q] ^ b[t][4 * h + q]);
+      }
+      const i32x4 a = wt(2 * t + h);
+      dx = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bx, dx, 0, 0, 0);
+      ds = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bs, ds, 0, 0, 0);
+    }
+  }
+  // lanes 0..15 hold digits 0..3 of their column's sum, lanes 16..31 digits
+  // 4..7, the others zeros
+  int64_t u = 0;
+#pragma unroll
+  for (int i = 3; i >= 0; --i) u = (u << 8) + (int64_t)(dx[i] - ds[i]);
+  uint64_t sum = (lane_id() & 16u) ? (uint64_t)u << 32 : (uint64_t)u;
+  sum *= colw;
+  sum += shfl_xor64(sum, 16);
+  sum += shfl_xor64(sum, 32);
+  if (ll > 2) sum += dpp64<0xb1>(sum);   // lane ^ 1
+  if (ll > 3) sum += dpp64<0x4e>(sum);   // lane ^ 2
+  if (ll > 4) sum += dpp64<0x141>(sum);  // the other four of eight
+  if (ll > 5) sum += dpp64<0x140>(sum);  // the other eight of sixteen
+  return sum;
+}
+
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
+// All 64 lanes of the wavefront call this.  Hashes items first, first + 1, ...
+// of groups of par_items(item_bytes), a group every `stride` items, up to
+// `cnt`: item i's bytes start at row0 + i * item_bytes and it has len_of(i) of
+// them (at most item_bytes, a multiple of 16).  done(i, h) is called by one
+// lane per item.  `tile`: this wavefront's kParTile bytes of LDS.  kAhead: the
+// next step's bytes are loaded while this one is hashed and the weights stay
+// in registers (work-groups of up to 512 work-items; wider ones have half the
+// registers per lane and more wavefronts to hide the loads).
+template <bool kAhead, class LenOf, class Done>
+__device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes, uint64_t first,
+                                             uint64_t stride, uint64_t cnt, uint8_t* tile_generic,
+                                             LenOf len_of, Done done) {
+  first = uniform64(first);
+  stride = uniform64(stride);
+  cnt = uniform64(cnt);
+  row0 = uniform64(row0);
+  if (first >= cnt) return;
+  lptr_t<uint8_t> tile = lp(tile_generic);
+  lptr_t<uint32_t> rlen = reinterpret_cast<lptr_t<uint32_t>>(tile + 64 * kSegStride);
+  const uint32_t lane = lane_id();
+  const uint32_t ll = par_lanes_log2(item_bytes), items = 64u >> ll;
+  const uint32_t n = lane & 15u, g = lane >> 4, seg = 4 * n + g;
+  // lanes with earlier bytes of the same item: the item's columns before this
+  // one, then this column's earlier quarters
+  const uint32_t col = n & ((16u >> (6 - ll)) - 1u);
+  const uint64_t colm = (uint64_t)((1u << n) - (1u << (n - col)));
+  uint64_t before = colm * 0x0001000100010001ull;
+  for (uint32_t k = 0; k < 3; ++k)
+    if (k < g) before |= 1ull << (16 * k + n);
+  const uint64_t colw = fnv_w.col[(16u >> (6 - ll)) - 1u - col];
+  const uint64_t slotw = fnv_w.seg[ll];
+  const uint64_t wbase = (uint64_t)&fnv_w.a[0][lane][0];
+  i32x4 held[8];
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) held[k] = *gp<const i32x4>(wbase + k * sizeof fnv_w.a[0]);
+  }
+  auto wt = [&](int k) -> i32x4 {
+    if constexpr (kAhead) return held[k];
+    uint64_t a = wbase + k * sizeof fnv_w.a[0];
+    asm("" : "+v"(a));  // loaded where it is used
+    return *gp<const i32x4>(a);
+  };
+  auto set_len = [&](uint32_t buf, uint64_t i0) {
+    if (lane < items) rlen[16 * buf + lane] = i0 + lane < cnt ? len_of(i0 + lane) : 0u;
+    __builtin_amdgcn_wave_barrier();
+  };
+  // Load k covers 1 KiB: part of one item, or two items' 512-byte slots.  A
+  // lane's place in it does not depend on k; the rest is the same in every
+  // lane.
+  const uint32_t two = ll == 2 ? lane >> 5 : 0u;
+  const uint32_t at = (lane * 16) & ((kSegBytes << ll) - 1u);
+  const uint32_t lane_off = two * item_bytes + at;
+  auto item_of = [&](uint32_t k) { return ll == 2 ? 2 * k : k >> (ll - 3); };
+  auto off_of = [&](uint32_t k) { return ll == 2 ? 0u : (k & ((1u << (ll - 3)) - 1u)) * 1024u; };
+  u32x4 v[8];
+  // bytes of the lane's item from the vector of load k on (<= 0: none)
+  auto left = [&](uint32_t k, uint32_t buf, uint32_t step) {
+    return (int32_t)(rlen[16 * buf + item_of(k) + two] - step * kStepBytes - off_of(k) - at);
+  };
+  // 16 bytes at a scalar address plus a 32-bit offset of the lane (opaque, so
+  // that no 64-bit address per load is kept in vector registers)
+  auto fetch = [&](uint64_t base, uint32_t voff) {
+    base = uniform64(base);
+    asm("" : "+s"(base));
+    return ldg16(base + voff);
+  };
+  // the step is consecutive bytes and all of them are there
+  auto whole = [&](uint32_t buf, uint32_t step) {
+    if (ll < 6 && item_bytes != kSegBytes << ll) return false;
+    const uint32_t need = ll == 6 ? (step + 1) * kStepBytes : item_bytes;
+    return __ballot(rlen[16 * buf + (lane & (items - 1u))] < need) == 0;
+  };
+  auto load_whole = [&](uint64_t i0, uint32_t step) {
+    const uint64_t p = row0 + i0 * item_bytes + step * kStepBytes;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) v[k] = fetch(p, k * 1024 + lane * 16);
+  };
+  // otherwise only vectors that hold bytes of an item are read, and the bytes
+  // past its end are cleared
+  auto load_part = [&](uint32_t buf, uint64_t i0, uint32_t step) {
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      v[k] = u32x4{0, 0, 0, 0};
+      if (left(k, buf, step) > 0)
+        v[k] = fetch(row0 + (i0 + item_of(k)) * item_bytes + step * kStepBytes + off_of(k), lane_off);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      const int32_t keep = left(k, buf, step);
+      if (keep > 0 && keep < 16)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          v[k][q] = keep >= 4 * q + 4 ? v[k][q]
+                    : keep <= 4 * q ? 0u : v[k][q] & ((1u << (8 * (keep - 4 * q))) - 1u);
+    }
+  };
+  uint32_t buf = 0;
+  set_len(0, first);
+  bool have = false;  // v holds the coming step's bytes
+  for (uint64_t i0 = first; i0 < cnt; i0 += stride) {
+    const uint32_t len = rlen[16 * buf + (seg >> ll)];
+    uint32_t steps = 1;
+    if (ll == 6) steps = max(1u, (__builtin_amdgcn_readfirstlane(len) + kStepBytes - 1) / kStepBytes);
+    const bool more = i0 + stride < cnt;
+    uint64_t h = kFnvBasis;
+    for (uint32_t st = 0; st < steps; ++st) {
+      if (!have) {
+        if (whole(buf, st)) load_whole(i0, st);
+        else load_part(buf, i0, st);
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) {
+        const uint32_t sg = k * 8 + (lane >> 3);
+        const uint32_t slot = (sg >> 2) + 16 * (sg & 3);  // the lane that hashes it
+        *reinterpret_cast<lptr_t<u32x4>>(tile + slot * kSegStride + (lane & 7u) * 16) = v[k];
+      }
+      __builtin_amdgcn_wave_barrier();
+      const bool same = st + 1 < steps;
+      if (!same && more) set_len(buf ^ 1u, i0 + stride);
+      if constexpr (kAhead) {
+        have = (same || more) && whole(same ? buf : buf ^ 1u, same ? st + 1 : 0u);
+        if (have) load_whole(same ? i0 : i0 + stride, same ? st + 1 : 0u);
+      }
+      uint32_t w[32];
+#pragma unroll
+      for (uint32_t q = 0; q < 8; ++q) {
+        const u32x4 m = *reinterpret_cast<lptr_t<const u32x4>>(tile + lane * kSegStride + q * 16);
+        w[4 * q] = m.x;
+        w[4 * q + 1] = m.y;
+        w[4 * q + 2] = m.z;
+        w[4 * q + 3] = m.w;
+      }
+      __builtin_amdgcn_wave_barrier();
+      h = h * slotw + par_step(w, (uint32_t)h & 0xffu, before, wt, colw, ll);
+    }
+    // undo the zero bytes after the item's end
+    uint32_t pad = ((kSegBytes << ll) * steps) - len;
+#pragma unroll 1
+    for (uint32_t k = 0; __ballot(pad != 0); ++k, pad >>= 1)
+      if (pad & 1u) h *= fnv_w.inv[k];
+    const uint64_t it = i0 + (seg >> ll);
+    if ((seg & ((1u << ll) - 1u)) == 0 && it < cnt) done(it, h);
+    buf ^= 1u;
+  }
 }
 
 }  // namespace gsys_k

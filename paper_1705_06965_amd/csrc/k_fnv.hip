@@ -5,9 +5,9 @@
 //
 // Data path: the host pool preads each item into pinned host staging; the GPU
 // reads the staging bytes once over the host link with coalesced 16-byte
-// loads (each group of 16 lanes fetches one item's next 256 bytes), transposes
-// them through LDS, and every lane runs the FNV-1a chain of its own item.
-// FNV-1a is a serial byte chain, so one lane per item is the parallel grain.
+// loads, transposes them through LDS and hashes them: items of more than 512
+// bytes with many lanes each (wave_fnv_par), shorter ones with a lane each
+// running the serial byte chain (wave_fnv_t).
 #include "gsys_device.hpp"
 #include "fnv_wave.hpp"
 #include "gsys.h"
@@ -38,7 +38,14 @@ struct FnvArgs {
   uint32_t item_bytes;
   uint32_t ring;  // persistent forms: 1 = each work-group owns two batch buffers
   uint32_t lds_list;  // strong work-group cells: aggregate the list in LDS first
+  uint32_t wg;     // work-items (and items) per work-group; wider blocks bring helper wavefronts
+  uint32_t batch;  // persistent forms: items per list call (at most wg)
 };
+
+// Threads of the widest block of a kernel variant: of the variants that hash
+// items with many lanes, up to 512 work-items hold the next step's bytes and
+// the weights in registers (256 per lane), wider ones do not (128 per lane).
+constexpr uint32_t kParBlock = 512;
 
 // Staging address of item `item` of batch `bt` (slot = item - bt * batch).
 __device__ __forceinline__ uint64_t stage_addr(const FnvArgs& A, uint64_t bt, uint32_t batch,
@@ -48,30 +55,57 @@ __device__ __forceinline__ uint64_t stage_addr(const FnvArgs& A, uint64_t bt, ui
   return A.staging + (buf * batch + (item - bt * batch)) * A.item_bytes;
 }
 
-// `row0` is the staging address of the item of lane 0 of this wavefront; the
-// wavefront's items follow it at item_bytes apart.
-template <uint32_t CH>
-__device__ __forceinline__ void consume_item(const FnvArgs& A, uint64_t item, bool valid,
-                                             int64_t ret, uint8_t* lds, uint64_t row0) {
-  const uint32_t wave = threadIdx.x >> 6;
+// The group's items first .. first + cnt - 1 (from staging address row0):
+// store each work-item's call result and hash the bytes.  `ret` is the result
+// of item first + threadIdx.x (cnt <= A.wg <= blockDim.x).  Serial: each
+// wavefront hashes its own 64 work-items' items.  Otherwise, in a block of
+// A.wg work-items each wavefront takes its own work-items' items too (no
+// wavefront waits for another's calls); in a wider block all wavefronts share
+// the group's items after a barrier.
+template <uint32_t WGMAX, bool par>
+__device__ __forceinline__ void consume_items(const FnvArgs& A, uint64_t first, uint32_t cnt,
+                                              int64_t ret, uint8_t* lds, uint64_t row0) {
+  const uint32_t t = threadIdx.x, wave = t >> 6;
+  const bool valid = t < cnt;
   const uint32_t nbytes =
       (valid && ret > 0) ? (uint32_t)min<int64_t>(ret, (int64_t)A.item_bytes) : 0u;
-  const uint64_t h = wave_fnv_t<CH>(row0, nbytes, A.item_bytes, lds + wave * Tile<CH>::kBytes);
-  if (valid) {
-    A.out_fnv[item] = h;
-    A.out_ret[item] = ret;
+  if (valid) A.out_ret[first + t] = ret;
+  if constexpr (!par) {
+    constexpr uint32_t CH = chunk_for<WGMAX>();
+    const uint64_t h = wave_fnv_t<CH>(row0 + (uint64_t)(t & ~63u) * A.item_bytes, nbytes,
+                                      A.item_bytes, lds + wave * Tile<CH>::kBytes);
+    if (valid) A.out_fnv[first + t] = h;
+  } else {
+    const uint32_t waves = blockDim.x >> 6, items = par_items(A.item_bytes);
+    lptr_t<uint32_t> lens = reinterpret_cast<lptr_t<uint32_t>>(lp(lds) + waves * kParTile);
+    if (t < A.wg) lens[t] = nbytes;
+    const bool shared = blockDim.x > A.wg;
+    uint32_t lo = 0, hi = cnt, step = waves * items;
+    if (shared) {
+      __syncthreads();
+      lo = wave * items;
+    } else {
+      __builtin_amdgcn_wave_barrier();
+      lo = wave * 64;
+      hi = min(cnt, lo + 64);
+      step = items;
+    }
+    wave_fnv_par<(WGMAX <= kParBlock)>(
+        row0, A.item_bytes, lo, step, hi, lds + wave * kParTile,
+        [&](uint64_t i) { return lens[i]; },
+        [&](uint64_t i, uint64_t h) { A.out_fnv[first + i] = h; });
   }
 }
 
 // Plain form: one launch, one item per work-item, the call made at the
 // granularity / ordering / blocking of the template.
-template <G g, O o, B b, uint32_t WGMAX>
-__global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_plain(FnvArgs A) {
-  constexpr uint32_t CH = chunk_for<WGMAX>();
+template <G g, O o, B b, uint32_t WGMAX, bool par>
+__global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_plain(FnvArgs A) {
   extern __shared__ __align__(16) uint8_t lds[];
-  const uint64_t first = (uint64_t)blockIdx.x * blockDim.x;
+  const uint64_t first = (uint64_t)blockIdx.x * A.wg;
   const uint64_t item = first + threadIdx.x;
-  const bool valid = item < A.n_items;
+  const uint32_t cnt = (uint32_t)min<uint64_t>(A.wg, A.n_items - first);
+  const bool valid = threadIdx.x < cnt;
   int64_t ret = 0;
   if constexpr (g == G::WorkItem) {
     if (valid) {
@@ -83,7 +117,6 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_plain(FnvAr
     }
   } else if constexpr (g == G::WorkGroup) {
     gsys_iodesc* L = A.lists + first;
-    const uint32_t cnt = (uint32_t)min<uint64_t>(blockDim.x, A.n_items - first);
     if constexpr (o == O::Strong) {
       const gsys_iodesc d{valid ? A.offsets[item] : 0, threadIdx.x * A.item_bytes,
                           (int32_t)A.item_bytes};
@@ -93,7 +126,7 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_plain(FnvAr
         // barrier the caller's wavefront copies the list to the host-visible
         // buffer with 16-byte stores; the call's barrier before releases them
         gsys_iodesc* S = reinterpret_cast<gsys_iodesc*>(lds);
-        *lp(reinterpret_cast<u32x4*>(S + threadIdx.x)) = *reinterpret_cast<const u32x4*>(&d);
+        if (valid) *lp(reinterpret_cast<u32x4*>(S + threadIdx.x)) = *reinterpret_cast<const u32x4*>(&d);
         __syncthreads();
         if (threadIdx.x < 64)
           for (uint32_t i = threadIdx.x; i < cnt; i += 64)
@@ -135,8 +168,7 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_plain(FnvAr
                                                           __HIP_MEMORY_SCOPE_SYSTEM))
                 : 0;
   }
-  const uint64_t row0 = A.staging + (first + (threadIdx.x & ~63u)) * A.item_bytes;
-  consume_item<CH>(A, item, valid, ret, lds, row0);
+  consume_items<WGMAX, par>(A, first, cnt, ret, lds, A.staging + first * A.item_bytes);
 }
 
 // Persistent form: a co-resident grid; work-group w handles batches w,
@@ -157,11 +189,10 @@ __device__ __forceinline__ Ticket issue_batch(const FnvArgs& A, uint64_t bt, uin
   return tk;
 }
 
-template <uint32_t WGMAX>
-__global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_persistent(FnvArgs A) {
-  constexpr uint32_t CH = chunk_for<WGMAX>();
+template <uint32_t WGMAX, bool par>
+__global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_persistent(FnvArgs A) {
   extern __shared__ __align__(16) uint8_t lds[];
-  const uint32_t batch = blockDim.x;
+  const uint32_t batch = A.batch;
   const uint64_t nb = (A.n_items + batch - 1) / batch;
   uint64_t bt = blockIdx.x;
   if (bt >= nb) return;
@@ -171,14 +202,14 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_persistent(
     Ticket tkn{0, 0, 0};
     if (bn < nb) tkn = issue_batch(A, bn, batch);
     const int64_t r = wait_wg(A.c, tk);
-    const uint64_t item = bt * batch + threadIdx.x;
-    const bool valid = item < A.n_items;
+    const uint64_t first = bt * batch;
+    const uint32_t cnt = (uint32_t)min<uint64_t>(batch, A.n_items - first);
     const int64_t ret =
-        valid ? (r < 0 ? r : (int64_t)__hip_atomic_load(&A.lists[item].len_ret, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_SYSTEM))
-              : 0;
-    const uint64_t row0 = stage_addr(A, bt, batch, bt * batch + (threadIdx.x & ~63u));
-    consume_item<CH>(A, item, valid, ret, lds, row0);
+        threadIdx.x < cnt
+            ? (r < 0 ? r : (int64_t)__hip_atomic_load(&A.lists[first + threadIdx.x].len_ret,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))
+            : 0;
+    consume_items<WGMAX, par>(A, first, cnt, ret, lds, stage_addr(A, bt, batch, first));
     // the buffer of batch bt is reused by batch bt + 2 * grid, issued in the
     // next iteration: every lane must be done reading it first
     __syncthreads();
@@ -206,6 +237,25 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_consume(
     const uint64_t h = wave_fnv_t<CH>(row0, nbytes, item_bytes, lds + wave * Tile<CH>::kBytes);
     if (valid) out_fnv[item] = h;
   }
+}
+
+// The same for items of more than 512 bytes: the launch's wavefronts take
+// par_items() items at a time.
+template <uint32_t WGMAX>
+__global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_consume_par(
+    uint64_t staging, const int64_t* rets, uint64_t n_items, uint32_t item_bytes,
+    uint64_t* out_fnv) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const uint32_t items = par_items(item_bytes);
+  wave_fnv_par<(WGMAX <= kParBlock)>(
+      staging, item_bytes, ((uint64_t)blockIdx.x * waves + wave) * items,
+      (uint64_t)gridDim.x * waves * items, n_items, lds + wave * kParTile,
+      [&](uint64_t i) {
+        const int64_t r = rets[i];
+        return r > 0 ? (uint32_t)min<int64_t>(r, (int64_t)item_bytes) : 0u;
+      },
+      [&](uint64_t i, uint64_t h) { out_fnv[i] = h; });
 }
 
 __global__ void zero_words(unsigned long long* p, uint32_t n) {
@@ -257,14 +307,30 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
     const char* e = getenv("GSYS_LDS_LISTS");
     A.lds_list = (e && *e == '0') ? 0u : 1u;
   }
+  A.wg = wg_size;
+  A.batch = wg_size;
   hipStream_t s = (hipStream_t)stream;
-  const bool small = wg_size <= 256;
-  const uint32_t lds = (wg_size / 64) * (small ? Tile<256>::kBytes : Tile<128>::kBytes);
+  // Many lanes per item, except in work-groups of 1,024 (128 registers per
+  // lane: they spill and load nothing ahead; 8,000 work-item preads of 4 KiB
+  // took 2.1 ms against 1.0 ms) unless the chain is long.
+  const bool par = item_bytes > (wg_size <= kParBlock ? kParMinItem : 16384u);
+  // the kernel variant's widest block: see kParBlock and chunk_for
+  const bool small = wg_size <= (par ? kParBlock : 256u);
+  uint32_t block = wg_size;
+  auto lds_for = [&](uint32_t threads) {
+    return par ? (threads / 64) * kParTile + wg_size * 4
+               : (threads / 64) * (small ? Tile<256>::kBytes : Tile<128>::kBytes);
+  };
 
   if (form == GSYS_PERSISTENT || form == GSYS_GRAPH) {
-    const uint64_t nb = (n_items + wg_size - 1) / wg_size;
-    const void* kp = small ? (const void*)fnv4k_persistent<256> : (const void*)fnv4k_persistent<1024>;
-    uint32_t grid = gsys_internal::resident_grid(ctx, kp, wg_size, lds);
+    if (par) block = std::max(block, 256u);
+    const uint32_t lds = lds_for(block);
+    const uint64_t nb = (n_items + A.batch - 1) / A.batch;
+    const void* kp = par ? (small ? (const void*)fnv4k_persistent<kParBlock, true>
+                                  : (const void*)fnv4k_persistent<1024, true>)
+                         : (small ? (const void*)fnv4k_persistent<256, false>
+                                  : (const void*)fnv4k_persistent<1024, false>);
+    uint32_t grid = gsys_internal::resident_grid(ctx, kp, block, lds);
     if (grid == 0) return -ENODEV;
     if ((uint64_t)grid > nb) grid = (uint32_t)nb;
     const uint32_t req = gsys_internal::persistent_grid_override(ctx);
@@ -275,16 +341,16 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
     if (staging_bytes < stage_bytes) {
       // staging ring: two batch buffers per resident work-group
       A.ring = 1;
-      const uint64_t fit = staging_bytes / (2 * batch_bytes);
+      const uint64_t fit = staging_bytes / (2ull * A.batch * item_bytes);
       if ((uint64_t)grid > fit) grid = (uint32_t)fit;
     }
     void* args[] = {&A};
     if (form == GSYS_GRAPH) {
-      const uint64_t key = gsys_internal::hash_words({0xF4Bull, (uint64_t)kp, grid, wg_size, lds});
-      const gsys_internal::KLaunch k{kp, dim3(grid), dim3(wg_size), lds, args};
+      const uint64_t key = gsys_internal::hash_words({0xF4Bull, (uint64_t)kp, grid, block, lds});
+      const gsys_internal::KLaunch k{kp, dim3(grid), dim3(block), lds, args};
       return gsys_internal::launch_graph(ctx, key, &k, 1, s);
     }
-    return gsys_internal::launch(ctx, kp, grid, wg_size, lds, args, s);
+    return gsys_internal::launch(ctx, kp, grid, block, lds, args, s);
   }
 
   const uint32_t gran = GSYS_CELL_GRAN(cell);
@@ -294,22 +360,27 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   if (grid64 > 0x7fffffffull) return -EINVAL;
   const uint32_t grid = (uint32_t)grid64;
   const void* k = nullptr;
+#define GSYS_PLAIN_K(G_, O_, B_)                                                   \
+  (par ? (small ? (const void*)fnv4k_plain<G_, O_, B_, kParBlock, true>            \
+                : (const void*)fnv4k_plain<G_, O_, B_, 1024, true>)                \
+       : (small ? (const void*)fnv4k_plain<G_, O_, B_, 256, false>                 \
+                : (const void*)fnv4k_plain<G_, O_, B_, 1024, false>))
   if (gran == GSYS_GRAN_WI) {
     if (!strong) return -EINVAL;  // work-item calls are implicitly strong
-    k = blocking ? (small ? (const void*)fnv4k_plain<G::WorkItem, O::Strong, B::Blocking, 256> : (const void*)fnv4k_plain<G::WorkItem, O::Strong, B::Blocking, 1024>)
-                 : (small ? (const void*)fnv4k_plain<G::WorkItem, O::Strong, B::NonBlocking, 256> : (const void*)fnv4k_plain<G::WorkItem, O::Strong, B::NonBlocking, 1024>);
+    k = blocking ? GSYS_PLAIN_K(G::WorkItem, O::Strong, B::Blocking)
+                 : GSYS_PLAIN_K(G::WorkItem, O::Strong, B::NonBlocking);
   } else if (gran == GSYS_GRAN_WG) {
     if (strong)
-      k = blocking ? (small ? (const void*)fnv4k_plain<G::WorkGroup, O::Strong, B::Blocking, 256> : (const void*)fnv4k_plain<G::WorkGroup, O::Strong, B::Blocking, 1024>)
-                   : (small ? (const void*)fnv4k_plain<G::WorkGroup, O::Strong, B::NonBlocking, 256> : (const void*)fnv4k_plain<G::WorkGroup, O::Strong, B::NonBlocking, 1024>);
+      k = blocking ? GSYS_PLAIN_K(G::WorkGroup, O::Strong, B::Blocking)
+                   : GSYS_PLAIN_K(G::WorkGroup, O::Strong, B::NonBlocking);
     else
-      k = blocking ? (small ? (const void*)fnv4k_plain<G::WorkGroup, O::Relaxed, B::Blocking, 256> : (const void*)fnv4k_plain<G::WorkGroup, O::Relaxed, B::Blocking, 1024>)
-                   : (small ? (const void*)fnv4k_plain<G::WorkGroup, O::Relaxed, B::NonBlocking, 256> : (const void*)fnv4k_plain<G::WorkGroup, O::Relaxed, B::NonBlocking, 1024>);
+      k = blocking ? GSYS_PLAIN_K(G::WorkGroup, O::Relaxed, B::Blocking)
+                   : GSYS_PLAIN_K(G::WorkGroup, O::Relaxed, B::NonBlocking);
   } else if (gran == GSYS_GRAN_KERNEL) {
     if (strong) return -EINVAL;  // kernel calls are relaxed only
     if (stage_bytes > 0xffffffffull) return -EINVAL;  // descriptor offsets are 32-bit
-    k = blocking ? (small ? (const void*)fnv4k_plain<G::Kernel, O::Relaxed, B::Blocking, 256> : (const void*)fnv4k_plain<G::Kernel, O::Relaxed, B::Blocking, 1024>)
-                 : (small ? (const void*)fnv4k_plain<G::Kernel, O::Relaxed, B::NonBlocking, 256> : (const void*)fnv4k_plain<G::Kernel, O::Relaxed, B::NonBlocking, 1024>);
+    k = blocking ? GSYS_PLAIN_K(G::Kernel, O::Relaxed, B::Blocking)
+                 : GSYS_PLAIN_K(G::Kernel, O::Relaxed, B::NonBlocking);
     // fresh per-launch state for the kernel-granularity call site
     if (gsys_internal::no_device(ctx)) return -ENODEV;
     hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, (unsigned long long*)A.ks,
@@ -318,8 +389,17 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   } else {
     return -EINVAL;
   }
+#undef GSYS_PLAIN_K
+  // Few work-groups leave compute units idle while theirs hash: helper
+  // wavefronts (they make no calls), up to eight per compute unit, share the
+  // group's items.  One work-group of 64 work-items and 64 items of 4 KiB:
+  // with its one wavefront about 55 us of hashing, with eight about 10.
+  if (par)
+    while (block * 2 <= kParBlock && (uint64_t)grid * block * 2 <=
+                                         (uint64_t)gsys_internal::cu_count(ctx) * kParBlock)
+      block *= 2;
   void* args[] = {&A};
-  return gsys_internal::launch(ctx, k, grid, wg_size, lds, args, s);
+  return gsys_internal::launch(ctx, k, grid, block, lds_for(block), args, s);
 }
 
 int gsys_fnv4k_consume(gsys_ctx* ctx, uint64_t staging, uint64_t rets, uint64_t n_items,
@@ -331,11 +411,37 @@ int gsys_fnv4k_consume(gsys_ctx* ctx, uint64_t staging, uint64_t rets, uint64_t 
   if (item_bytes == 0 || item_bytes % 64 || item_bytes > (1u << 20)) return -EINVAL;
   if (!(wg_size == 64 || wg_size == 128 || wg_size == 256 || wg_size == 512 || wg_size == 1024))
     return -EINVAL;
+  void* args[] = {&staging, &rets, &n_items, &item_bytes, &out_fnv};
+  hipStream_t s = (hipStream_t)stream;
+  // Many lanes per item, unless there are enough items for the serial chains
+    // to fill the chip (65,536 lanes' worth) and the items leave much of their
+  // lanes' bytes empty.  The weights are the measured costs per byte: dense
+  // items 27 cycles, others 40 (they are not loaded ahead), the chain 32.
+  const uint64_t slot = std::max<uint64_t>(item_bytes, (uint64_t)kSegBytes << par_lanes_log2(item_bytes));
+  const double par_cost = (double)n_items * slot * (slot == item_bytes ? 27 : 40);
+  const double serial_cost = 32.0 * item_bytes * (double)std::max<uint64_t>(n_items, 65536);
+  if (item_bytes > kParMinItem && par_cost < serial_cost) {
+    // grid 0: four wavefronts per work-group, each with work, as many as run
+    // at once; otherwise the caller's grid of wg_size work-items each
+    const bool wide = grid && wg_size > kParBlock;
+    const uint32_t block = grid ? wg_size : 256;
+    const uint32_t lds = (block / 64) * kParTile;
+    const void* k = wide ? (const void*)fnv4k_consume_par<1024>
+                         : (const void*)fnv4k_consume_par<kParBlock>;
+    const uint64_t per = (uint64_t)(block / 64) * par_items(item_bytes);
+    const uint64_t nb = (n_items + per - 1) / per;
+    if (!grid) {
+      if (gsys_internal::no_device(ctx)) return -ENODEV;
+      grid = gsys_internal::resident_grid(ctx, k, block, lds);
+      if (!grid) return -ENODEV;
+    }
+    if (grid > nb) grid = (uint32_t)nb;
+    return gsys_internal::launch(ctx, k, grid, block, lds, args, s);
+  }
   const uint64_t nb = (n_items + wg_size - 1) / wg_size;
   if (!grid || grid > nb) grid = (uint32_t)std::min<uint64_t>(nb, 0x7fffffffull);
   const bool small = wg_size <= 256;
   const uint32_t lds = (wg_size / 64) * (small ? Tile<256>::kBytes : Tile<128>::kBytes);
-  void* args[] = {&staging, &rets, &n_items, &item_bytes, &out_fnv};
   const void* k = small ? (const void*)fnv4k_consume<256, 256> : (const void*)fnv4k_consume<1024, 128>;
-  return gsys_internal::launch(ctx, k, grid, wg_size, lds, args, (hipStream_t)stream);
+  return gsys_internal::launch(ctx, k, grid, wg_size, lds, args, s);
 }

@@ -19,6 +19,8 @@ void* kstate(gsys_ctx* ctx);
 uint32_t resident_grid(gsys_ctx* ctx, const void* kernel, uint32_t block, uint32_t lds);
 // A persistent grid size requested through GSYS_PERSISTENT_GRID (0 = none).
 uint32_t persistent_grid_override(gsys_ctx* ctx);
+// Compute units of the context's device.
+uint32_t cu_count(gsys_ctx* ctx);
 uint64_t hash_words(std::initializer_list<uint64_t> w);
 // Two host-coherent control words owned by the context (a 256-byte line of
 // the page set up by gsys_init; nothing is allocated here).
