@@ -299,13 +299,15 @@ const char *gsys_strerror(int code);
  *   cell      GSYS_CELL_* bits; work-item must be strong and kernel must be
  *             relaxed (section 4.1), others give -EINVAL
  *   form      GSYS_PLAIN (grid n_items / wg_size) or GSYS_PERSISTENT /
- *             GSYS_GRAPH (co-resident grid looping over batches of wg_size
- *             items, double-buffered non-blocking group calls; cell ignored).
+ *             GSYS_GRAPH (co-resident grid looping over batches of at most
+ *             wg_size items, double-buffered non-blocking group calls; a
+ *             batch is one list call of at most 256 items and 256 KiB, shorter
+ *             when there are few items; cell ignored).
  *             The persistent grid is 64 work-groups (fewer if fewer are
  *             resident or there are fewer batches; environment
  *             GSYS_PERSISTENT_GRID sets it instead): every work-group waiting
  *             for its call polls host memory, which slows the host pool, and
- *             64 groups of 256 keep enough reads in flight.
+ *             64 groups keep enough reads in flight.
  *   wg_size   work-items per work-group: 64, 128, 256, 512 or 1024.  A launch
  *             may give its work-groups further wavefronts that make no calls
  *             and help to hash (items of more than 512 bytes).

@@ -19,10 +19,10 @@ namespace gsys_k {
 
 using namespace gsys;
 
-// Default persistent grid (work-groups); see gsys_fnv4k.  With 256-wide
-// groups, 64 keep 32,768 reads in flight, which is enough for the host pool,
-// and fewer waiters poll host memory: on the 262,144-item sweep 64 ran at
-// 13.4 M calls/s against 12.8 M with 128 and 12.5 M with 256.
+// Default persistent grid (work-groups); see gsys_fnv4k.  64 of them keep 128
+// lists in flight, which is enough for the host pool, and fewer waiters poll
+// host memory: the 262,144-item sweep took 19.7 ms with 64 or 48, 20.0 with
+// 32 and 19.8 with 80 to 128.
 constexpr uint32_t kPersistentGrid = 64;
 
 struct FnvArgs {
@@ -39,7 +39,7 @@ struct FnvArgs {
   uint32_t ring;  // persistent forms: 1 = each work-group owns two batch buffers
   uint32_t lds_list;  // strong work-group cells: aggregate the list in LDS first
   uint32_t wg;     // work-items (and items) per work-group; wider blocks bring helper wavefronts
-  uint32_t batch;  // persistent forms: items per list call (at most wg)
+  uint32_t batch;  // persistent forms: items per list call (wg is the same)
 };
 
 // Threads of the widest block of a kernel variant: of the variants that hash
@@ -172,8 +172,8 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_plain
 }
 
 // Persistent form: a co-resident grid; work-group w handles batches w,
-// w + grid, ...; each batch is one work-group call (relaxed consumer,
-// non-blocking) whose descriptor list the caller's wavefront builds.  The
+// w + grid, ...; each batch of A.batch items is one work-group call (relaxed
+// consumer, non-blocking) whose descriptor list the caller's wavefront builds.  The
 // call for the next batch is issued before waiting on the current one, so
 // host servicing overlaps the GPU's consumption.
 __device__ __forceinline__ Ticket issue_batch(const FnvArgs& A, uint64_t bt, uint32_t batch) {
@@ -190,7 +190,7 @@ __device__ __forceinline__ Ticket issue_batch(const FnvArgs& A, uint64_t bt, uin
 }
 
 template <uint32_t WGMAX, bool par>
-__global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_persistent(FnvArgs A) {
+__global__ __launch_bounds__(WGMAX, 2) void fnv4k_persistent(FnvArgs A) {
   extern __shared__ __align__(16) uint8_t lds[];
   const uint32_t batch = A.batch;
   const uint64_t nb = (A.n_items + batch - 1) / batch;
@@ -313,23 +313,39 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   // Many lanes per item, except in work-groups of 1,024 (128 registers per
   // lane: they spill and load nothing ahead; 8,000 work-item preads of 4 KiB
   // took 2.1 ms against 1.0 ms) unless the chain is long.
-  const bool par = item_bytes > (wg_size <= kParBlock ? kParMinItem : 16384u);
+  bool par = item_bytes > (wg_size <= kParBlock ? kParMinItem : 16384u);
   // the kernel variant's widest block: see kParBlock and chunk_for
-  const bool small = wg_size <= (par ? kParBlock : 256u);
+  bool small = wg_size <= (par ? kParBlock : 256u);
   uint32_t block = wg_size;
   auto lds_for = [&](uint32_t threads) {
-    return par ? (threads / 64) * kParTile + wg_size * 4
+    return par ? (threads / 64) * kParTile + A.wg * 4
                : (threads / 64) * (small ? Tile<256>::kBytes : Tile<128>::kBytes);
   };
 
   if (form == GSYS_PERSISTENT || form == GSYS_GRAPH) {
-    if (par) block = std::max(block, 256u);
-    const uint32_t lds = lds_for(block);
+    // Lists of at most 256 items and 256 KiB: one service thread runs a list,
+    // so the first bytes cross the link a list's service time after the start
+    // and the last list is hashed after the link is done.  A launch of few
+    // items takes shorter ones still, at least 128 (two per work-group of the
+    // default grid) so that every service thread has several, down to 64 KiB.
+    // 1 GiB in 4 KiB items: 20.2 ms with 1 MiB lists, 20.1 with 512 KiB, 19.9
+    // with 256 KiB, 20.0 with 128 KiB; 5,003 items: 585 us with 1 MiB, 495
+    // with 256 KiB, 485 with 128 KiB, 494 with 64 KiB, 554 with 32 KiB.
+    A.batch = std::min(wg_size, 256u);
+    while (A.batch > 1 && (uint64_t)A.batch * item_bytes > 262144) A.batch = (A.batch + 1) / 2;
+    while (A.batch > 1 && n_items < 128ull * A.batch && (uint64_t)A.batch * item_bytes > 65536)
+      A.batch = (A.batch + 1) / 2;
+    A.wg = A.batch;
     const uint64_t nb = (n_items + A.batch - 1) / A.batch;
-    const void* kp = par ? (small ? (const void*)fnv4k_persistent<kParBlock, true>
-                                  : (const void*)fnv4k_persistent<1024, true>)
-                         : (small ? (const void*)fnv4k_persistent<256, false>
-                                  : (const void*)fnv4k_persistent<1024, false>);
+    // Eight wavefronts hash a list sooner, four leave the link and the pool
+    // more to the others: 25,000 items of 4 KiB (391 lists) take 2.03 against
+    // 2.08 ms, 60,000 (938) 4.63 either way, 262,144 19.9 either way.
+    par = item_bytes > kParMinItem;
+    block = par && nb <= 1024 ? kParBlock : 256;
+    small = true;
+    const uint32_t lds = lds_for(block);
+    const void* kp = par ? (const void*)fnv4k_persistent<kParBlock, true>
+                         : (const void*)fnv4k_persistent<256, false>;
     uint32_t grid = gsys_internal::resident_grid(ctx, kp, block, lds);
     if (grid == 0) return -ENODEV;
     if ((uint64_t)grid > nb) grid = (uint32_t)nb;
