@@ -22,6 +22,7 @@
 //    append to (or consume) the file in launch order.
 #include "gsys_device.hpp"
 #include "gsys.h"
+#include "host_copy.hpp"
 #include "kernels.hpp"
 
 #include <fcntl.h>
@@ -31,6 +32,7 @@
 namespace gsys_fio {
 
 using namespace gsys;
+using namespace gsys_hc;
 
 constexpr uint32_t kWG = 256;
 constexpr uint32_t kEofRead = 16;  // bytes asked for by the read at the end of the file
@@ -49,41 +51,10 @@ struct RtArgs {
   int32_t dirfd;
 };
 
-// Copies and compares between host staging and HBM.  The host side of every
-// 16-byte vector is aligned (the bytes before the first such address and after
-// the last are done one by one); the HBM side may lie at any byte address, as
-// pieces of odd length do (a global load needs no alignment).  Each work-item
-// keeps kDeep vectors in flight: the staging side is a host-link round trip of
-// about 2 us, so what one work-group moves is bound by the bytes it keeps in
-// flight (256 work-items x 8 x 16 B = 32 KiB), not by the link.  With one
-// byte per work-item, the round trip of 64 files x 4 MiB in 1 MiB pieces took
-// 34.8 ms, most of it in the compare; with these and the compare overlapped
-// with the reads it takes 15.0 ms, bound by the host's write() and read().
-constexpr uint32_t kDeep = 8;
-typedef u32x4 u32x4_u __attribute__((aligned(1)));
-__device__ __forceinline__ u32x4 ldg16_any(const uint8_t* p) { return *gp<const u32x4_u>((uint64_t)p); }
-
-// Bytes of [0, n) before the first 16-byte boundary at or after `a`.
-__device__ __forceinline__ uint64_t head_bytes(uint64_t a, uint64_t n) {
-  return min<uint64_t>(n, (0 - a) & 15);
-}
-
-// Work-items 0 .. nt - 1 copy n bytes from HBM to host staging.
-__device__ void copy_to_host(uint64_t dst, const uint8_t* src, uint64_t n, uint32_t t,
-                             uint32_t nt) {
-  const uint64_t h = head_bytes(dst, n), nv = (n - h) / 16, tail = h + nv * 16;
-  if (t < h) gp<uint8_t>(dst)[t] = gp(src)[t];
-  uint64_t i = t;
-  for (; i + (kDeep - 1) * (uint64_t)nt < nv; i += kDeep * (uint64_t)nt) {
-    u32x4 v[kDeep];
-#pragma unroll
-    for (uint32_t k = 0; k < kDeep; ++k) v[k] = ldg16_any(src + h + 16 * (i + k * (uint64_t)nt));
-#pragma unroll
-    for (uint32_t k = 0; k < kDeep; ++k) stg16(dst + h + 16 * (i + k * (uint64_t)nt), v[k]);
-  }
-  for (; i < nv; i += nt) stg16(dst + h + 16 * i, ldg16_any(src + h + 16 * i));
-  if (tail + t < n) gp<uint8_t>(dst)[tail + t] = gp(src)[tail + t];
-}
+// Copies are host_copy.hpp's.  The compare over the same 16-byte vectors, one
+// byte per work-item before: 64 files x 4 MiB in 1 MiB pieces took 34.8 ms,
+// most of it in the compare; with these and the compare overlapped with the
+// reads 15.0 ms, bound by the host's write() and read().
 
 // Bytes of x that are not zero.
 __device__ __forceinline__ uint32_t nonzero_bytes(u32x4 x) {

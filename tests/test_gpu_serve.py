@@ -313,3 +313,45 @@ def test_full_session_in_the_benchmark_configuration(gs, tmpdata):
         want, _ = oracle.pread_fnv(in_path, offs, 4096, threads=8)
         d0 = int(sr.digest_start[i])
         assert (dig[d0:d0 + nb] == want).all(), i
+
+
+@pytest.mark.parametrize("form", ["persistent", "plain"])
+def test_scan_pieces_both_hashes(gs, tmpdata, form):
+    """Scans whose last piece lies on both sides of the rule between many
+    lanes per block and one (192 blocks), and whose range ends past the end of
+    the file; pwrites at every source alignment and around vector edges."""
+    g, ctx = gs
+    from paper_1705_06965_amd.serve import ServeRun
+    in_path = synth.random_file(5, 64 << 20, name="c5_in_64m.bin")
+    pages = np.array([1, 2, 7, 64, 191, 192, 193, 255, 256, 257, 447, 448, 449, 513, 200, 100])
+    n, w = len(pages), 24
+    size = 64 << 20
+    off = (np.arange(n) * 1_372_160 // 4096 * 4096).astype(np.uint64)
+    off[-2:] = size - 4096 * np.array([150, 3])  # ranges that run past the end
+    wlen = np.array([1, 15, 16, 17, 31, 4095, 4096, 4099] * 3, dtype=np.uint64)
+    content = np.random.default_rng(7).integers(0, 256, int(wlen.sum()) + 64, dtype=np.uint8)
+    js = synth.JobStream(
+        kind=np.array([0] * n + [1] * w, dtype=np.uint8),
+        arrival_ns=np.zeros(n + w, dtype=np.uint64),
+        arg_off=np.concatenate([off, np.arange(w, dtype=np.uint64) * 8192 + 3]),
+        arg_len=np.concatenate([pages.astype(np.uint64) * 4096, wlen]),
+        content_off=np.concatenate([np.zeros(n, dtype=np.uint64),
+                                    np.cumsum(wlen) - wlen + np.arange(w, dtype=np.uint64)]),
+        content=content)
+    out_path = os.path.join(tmpdata, "serve_pieces_%s.bin" % form)
+    sr = ServeRun(ctx, js, in_path, out_path)
+    say("serve pieces", form)
+    res, dig, _ = sr.run(g.PERSISTENT if form == "persistent" else g.PLAIN, max_inflight=64,
+                         staging_bytes=(2 << 20) * 16)
+    sr.close()
+    out = np.fromfile(out_path, dtype=np.uint8)
+    for i in range(n):
+        have = min(int(pages[i]) * 4096, size - int(off[i]))
+        assert res[i] == have
+        want, _ = oracle.pread_fnv(in_path, off[i] + 4096 * np.arange(int(pages[i]), dtype=np.uint64),
+                                   4096)
+        d0 = int(sr.digest_start[i])
+        assert (dig[d0:d0 + len(want)] == want).all(), (i, pages[i])
+    for i in range(w):
+        o, ln, src = int(js.arg_off[n + i]), int(wlen[i]), int(js.content_off[n + i])
+        assert res[n + i] == ln and (out[o:o + ln] == content[src:src + ln]).all(), i
