@@ -10,15 +10,21 @@
 // token); a token belongs to the chunk in which it starts.  The persistent
 // form takes chunks from a device work counter and prefetches the next one.
 //
-// Each chunk is scanned from LDS in 32 KiB sub-blocks, streamed from host
-// staging with fully coalesced 16-byte loads (the next sub-block's loads are
-// in flight while the current one is scanned).  Every lane owns a 64-byte
-// stretch: it builds a 64-bit delimiter mask with byte-parallel compares,
-// walks the token starts in its stretch with count-trailing-zeros, and for a
-// token of at most 16 bytes assembles its bytes from aligned LDS words with
-// alignbyte.  The (zero-padded) 16 bytes and the length are looked up in an
-// LDS hash table of the queries and compared exactly; matches are counted in
-// per-wavefront LDS counters and added to counts[file] once per chunk.
+// Each wavefront scans 4 KiB sub-blocks of the chunk by itself (no work-group
+// barrier inside a chunk), streamed from host staging with coalesced 16-byte
+// loads (the next sub-block's loads are in flight while the current one is
+// scanned).  A lane turns the vectors it loaded into delimiter bits with
+// byte-parallel compares and puts both in LDS; then every lane owns a 64-byte
+// stretch and packs the positions of its token starts into one list of the
+// wavefront, so that the lanes share the tokens evenly.  Each token's length
+// comes from the delimiter bits after its start; one of at most 16 bytes is
+// tested, by its first four bytes and its length, against a 2,048-bit filter
+// of the queries.  What passes is appended to a list of
+// the wavefront, and whenever 64 tokens are listed each lane takes one: its
+// (zero-padded) 16 bytes, assembled from aligned LDS words with alignbyte,
+// and its length are looked up in an LDS hash table of the queries and
+// compared exactly; matches are counted in per-wavefront LDS counters and
+// added to counts[file] once per chunk.
 #include "gsys_device.hpp"
 #include "gsys.h"
 #include "kernels.hpp"
@@ -31,20 +37,21 @@ namespace gsys_ws {
 
 using namespace gsys;
 
-// 512-wide work-groups: each one keeps a 32 KiB sub-block of host staging in
-// flight while it scans the previous one.  Fewer, wider groups (64 of them
-// with 128 chunk buffers) scan the 2,000-file corpus at 51 GB/s against 47 GB/s
-// for 128 groups of 256 with the same bytes in flight.
-constexpr uint32_t kWG = 512;
+// Work-groups of 512 (eight 4 KiB sub-blocks of host staging in flight while
+// the previous ones are scanned) scan the 2,000-file corpus as fast as the
+// link delivers it: 4.27 ms with 64 of them and 128 chunk buffers, against
+// 4.49 ms with work-groups of 1,024, whose loads slow the host pool.  Where no
+// work-group has a second chunk or file to go on with, a launch lasts as long
+// as its longest one and 1,024 scan it sooner: 40 files by name 338 -> 285 us.
+constexpr uint32_t kNarrow = 512, kWide = 1024;
 constexpr uint32_t kSeg = 64;                 // bytes scanned per lane per sub-block
-constexpr uint32_t kSB = kWG * kSeg;          // 32 KiB sub-block
+constexpr uint32_t kSB = 64 * kSeg;           // 4 KiB sub-block of a wavefront
 constexpr uint32_t kOverlap = 16;             // max query length and read-ahead
 constexpr uint32_t kHead = 16;                // staging bytes before chunk byte 0
-constexpr uint32_t kCopy = kSB + 48;          // LDS bytes per sub-block (look-behind + halo)
-constexpr uint32_t kCopyVec = kCopy / 16;     // 16-byte loads per sub-block
-constexpr uint32_t kPerLane = (kCopyVec + kWG - 1) / kWG;
+constexpr uint32_t kVecs = (kHead + kSB + kOverlap) / 16;  // 16-byte vectors per sub-block
 constexpr uint32_t kMaxQ = 64;
 constexpr uint32_t kTab = 128;                // query hash table slots
+constexpr uint32_t kFilter = 2048;            // filter bits
 
 struct WsArgs {
   gsys_dev_ctx c;
@@ -60,64 +67,107 @@ struct WsArgs {
   uint32_t passes;          // persistent forms: scans of every chunk in one launch
 };
 
+// One wavefront's sub-block: its bytes (16 before the first position, 16 after
+// the last, and the rest of the last token's aligned words), the delimiter
+// bits of vector i in bits[i + 3] (so that a lane's 64 bits are one aligned
+// word: position p is bit p + 64), and the tokens that passed the filter
+// (position | length << 16).
+struct __align__(16) WaveBuf {
+  uint8_t buf[kVecs * 16 + 16];
+  uint16_t bits[kVecs + 3 + 3];
+  uint32_t list[64 + 2 * 64];
+  uint16_t starts[kSB / 2];   // positions of the sub-block's token starts
+};
+
+typedef uint64_t __attribute__((may_alias)) u64_any;  // several of `bits` at once
+typedef uint32_t __attribute__((may_alias)) u32_any;
+
+template <uint32_t WG>
 struct Shared {
-  uint8_t buf[kCopy];
-  uint4 qw[kTab];           // query bytes per slot, zero-padded to 16
+  static constexpr uint32_t kWaves = WG / 64;
+  WaveBuf wb[kWaves];
+  u32x4 qw[kTab];           // query bytes per slot, zero-padded to 16
+  u32x4 mask[kOverlap + 1]; // the first n bytes of 16
   uint32_t tkey[kTab];      // hash key per slot; 0 = empty
   int32_t tq[kTab];         // query index | length << 16 per slot
-  uint32_t cnt[kWG / 64][kMaxQ];
+  uint32_t filter[kFilter / 32];
+  uint32_t cnt[kWaves][kMaxQ];
   uint32_t next;
 };
 
 // Key of a token or query: its (zero-padded) 16 bytes and length mixed into
 // 32 bits; never 0.  Equal strings have equal keys; a key match is confirmed
 // by comparing all 16 bytes and the length.
-__device__ __forceinline__ uint32_t token_key(uint4 w, uint32_t len) {
-  uint32_t h = len * 0x9e3779b1u;
-  h = (h ^ w.x) * 0x85ebca6bu;
-  h = (h ^ (h >> 15) ^ w.y) * 0xc2b2ae35u;
-  h = (h ^ (h >> 13) ^ w.z) * 0x27d4eb2fu;
-  h = (h ^ (h >> 16) ^ w.w) * 0x165667b1u;
-  h ^= h >> 15;
-  return h | 1u;
+__device__ __forceinline__ uint32_t token_key(u32x4 w, uint32_t len) {
+  const uint32_t r = w.x ^ __builtin_amdgcn_alignbit(w.y, w.y, 25) ^
+                     __builtin_amdgcn_alignbit(w.z, w.z, 18) ^ __builtin_amdgcn_alignbit(w.w, w.w, 11);
+  const uint32_t h = (r ^ (len << 3)) * 0x9e3779b1u;
+  return (h ^ (h >> 15)) | 1u;
 }
 
-__device__ __forceinline__ uint32_t mask_bytes(uint32_t x, int32_t keep) {
-  // keep the low `keep` bytes of x (keep <= 0: none, >= 4: all)
-  return keep >= 4 ? x : (keep <= 0 ? 0u : (x & ((1u << (8 * keep)) - 1u)));
+// The low `keep` bytes of a word (keep <= 0: none, >= 4: all).
+__device__ __forceinline__ uint32_t byte_mask(int32_t keep) {
+  return keep >= 4 ? ~0u : (keep <= 0 ? 0u : (1u << (8 * keep)) - 1u);
 }
 
-__device__ void build_table(const WsArgs& A, Shared& S) {
-  for (uint32_t i = threadIdx.x; i < kTab; i += blockDim.x) {
-    S.tkey[i] = 0;
-    S.tq[i] = -1;
+// Filter bit of a string from its first four bytes (those past its length
+// shifted out) and its length.
+__device__ __forceinline__ uint32_t filter_bit(uint32_t w0, uint32_t len) {
+  const uint32_t k = w0 << (len >= 4 ? 0u : 32 - 8 * len);
+  return ((k ^ (len << 3)) * 0x9e3779b1u) >> (32 - 11);
+}
+static_assert(kFilter == 1u << 11, "filter_bit gives 11 bits");
+
+// Clear the counters and build the query table and filter.  The second
+// wavefront does it, so that the first can issue the first call meanwhile;
+// the caller's next work-group barrier ends it.
+template <uint32_t WG>
+__device__ void build_table(const WsArgs& A, Shared<WG>& S) {
+  if (threadIdx.x >= 128)
+    for (uint32_t i = threadIdx.x - 128; i < (WG / 64) * kMaxQ; i += WG - 128) (&S.cnt[0][0])[i] = 0;
+  if (threadIdx.x < 64 || threadIdx.x >= 128) return;
+  const uint32_t q = threadIdx.x - 64;
+  static_assert(kTab == 128 && kFilter == 64 * 32 && kMaxQ == 64, "one wavefront's shares");
+  S.tkey[q] = 0;
+  S.tkey[q + 64] = 0;
+  S.tq[q] = -1;
+  S.tq[q + 64] = -1;
+  S.filter[q] = 0;
+  if (q <= kOverlap)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S.mask[q][i] = byte_mask((int32_t)q - 4 * i);
+  __builtin_amdgcn_wave_barrier();
+  if (q < A.nq) {
+    const uint32_t len = A.qlens[q];
+    const uint32_t* qp = reinterpret_cast<const uint32_t*>(A.queries + q * 16);
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = qp[i] & byte_mask((int32_t)len - 4 * i);
+    const uint32_t k = token_key(w, len);
+    uint32_t s = k & (kTab - 1);
+    while (atomicCAS(&S.tkey[s], 0u, k) != 0u) s = (s + 1) & (kTab - 1);
+    S.tq[s] = (int32_t)(q | (len << 16));
+    S.qw[s] = w;
+    const uint32_t f = filter_bit(w.x, len);
+    atomicOr(&S.filter[f >> 5], 1u << (f & 31u));
   }
-  for (uint32_t i = threadIdx.x; i < (kWG / 64) * kMaxQ; i += blockDim.x) (&S.cnt[0][0])[i] = 0;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (uint32_t q = 0; q < A.nq; ++q) {
-      const uint32_t len = A.qlens[q];
-      const uint32_t* qp = reinterpret_cast<const uint32_t*>(A.queries + q * 16);
-      uint4 w = make_uint4(mask_bytes(qp[0], (int32_t)len), mask_bytes(qp[1], (int32_t)len - 4),
-                           mask_bytes(qp[2], (int32_t)len - 8), mask_bytes(qp[3], (int32_t)len - 12));
-      const uint32_t k = token_key(w, len);
-      uint32_t s = k & (kTab - 1);
-      while (S.tkey[s]) s = (s + 1) & (kTab - 1);
-      S.tkey[s] = k;
-      S.tq[s] = (int32_t)(q | (len << 16));
-      S.qw[s] = w;
-    }
-  }
-  __syncthreads();
 }
 
-// 4-bit mask of the bytes of x equal to space or newline (bit j = byte j).
-__device__ __forceinline__ uint32_t delim4(uint32_t x) {
-  auto zero_bytes = [](uint32_t v) {  // 0x80 in every byte of v that is zero
-    return ~(((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u;
-  };
-  const uint32_t z = zero_bytes(x ^ 0x20202020u) | zero_bytes(x ^ 0x0a0a0a0au);
-  return ((z >> 7) & 1u) | ((z >> 14) & 2u) | ((z >> 21) & 4u) | ((z >> 28) & 8u);
+// The bytes of x equal to space or newline, as bits weighted by wt's bytes and
+// added to acc.
+__device__ __forceinline__ uint32_t delim_bits(uint32_t x, uint32_t wt, uint32_t acc) {
+  const uint32_t a = x ^ 0x20202020u, b = x ^ 0x0a0a0a0au;
+  // 0x80 in every byte that is not zero
+  const uint32_t na = ((a & 0x7f7f7f7fu) + 0x7f7f7f7fu) | a;
+  const uint32_t nb = ((b & 0x7f7f7f7fu) + 0x7f7f7f7fu) | b;
+  return __builtin_amdgcn_udot4((~(na & nb) >> 7) & 0x01010101u, wt, acc, false);
+}
+
+// 16 delimiter bits of a 16-byte vector (bit j = byte j).
+__device__ __forceinline__ uint32_t delim16(u32x4 v) {
+  const uint32_t lo = delim_bits(v.y, 0x80402010u, delim_bits(v.x, 0x08040201u, 0));
+  const uint32_t hi = delim_bits(v.w, 0x80402010u, delim_bits(v.z, 0x08040201u, 0));
+  return lo | (hi << 8);
 }
 
 // Staging buffer `slot` holds one chunk: byte k of the chunk at kHead + k and
@@ -133,20 +183,67 @@ __device__ Ticket issue_chunk(const WsArgs& A, uint32_t ci, uint64_t slot) {
   return tk;
 }
 
-// Load this lane's share of the sub-block at staging byte sb0 (bytes
-// [sb0, sb0 + kCopy) from stg) into registers.  Only 16-byte vectors that lie
+// This lane's vectors of the sub-block at staging byte sb0: vector i covers
+// bytes sb0 + 16 i of stg, lane l has vectors l + 64 k.  Only vectors that lie
 // inside the buffer (`lim` bytes from stg) and start before `data` (the end of
 // the bytes the call returned) cross the host link; the rest read as spaces,
 // which the scan treats as delimiters, as it does every position past the
 // valid extent.
+constexpr uint32_t kPerLane = (kVecs + 63) / 64;
 __device__ __forceinline__ void load_sub(const uint8_t* stg, uint32_t lim, uint32_t data,
-                                         uint32_t sb0, uint4 (&v)[kPerLane]) {
+                                         uint32_t sb0, u32x4 (&v)[kPerLane]) {
+  const uint32_t lane = lane_id();
 #pragma unroll
   for (uint32_t k = 0; k < kPerLane; ++k) {
-    const uint32_t i = threadIdx.x + k * kWG;
-    v[k] = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
-    if (i < kCopyVec && sb0 + i * 16 + 16 <= lim && sb0 + i * 16 < data)
-      v[k] = to_uint4(ldg16((uint64_t)(stg + sb0 + i * 16)));
+    const uint32_t i = lane + k * 64;
+    v[k] = u32x4{0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u};
+    if (i < kVecs && sb0 + i * 16 + 16 <= lim && sb0 + i * 16 < data)
+      v[k] = ldg16((uint64_t)(stg + sb0 + i * 16));
+  }
+}
+
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr 1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast 15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast 31
+  return v;
+}
+
+// The first dword of the (unaligned) text at buf + pos.
+__device__ __forceinline__ uint32_t text4(lptr_t<const uint8_t> buf, uint32_t pos) {
+  lptr_t<const uint32_t> a = reinterpret_cast<lptr_t<const uint32_t>>(buf + (pos & ~3u));
+  return __builtin_amdgcn_alignbyte(a[1], a[0], pos & 3u);
+}
+
+// Look the token at buf + pos up and count it (lanes with len == 0 hold none).
+template <class Sh>
+__device__ __forceinline__ void count_token(Sh& S, uint32_t wave, lptr_t<const uint8_t> buf,
+                                            uint32_t pos, uint32_t len) {
+  if (!len) return;
+  lptr_t<const uint32_t> aw = reinterpret_cast<lptr_t<const uint32_t>>(buf + (pos & ~3u));
+  const uint32_t sh = pos & 3u;
+  const uint32_t a0 = aw[0], a1 = aw[1], a2 = aw[2], a3 = aw[3], a4 = aw[4];
+  const u32x4 w = u32x4{__builtin_amdgcn_alignbyte(a1, a0, sh), __builtin_amdgcn_alignbyte(a2, a1, sh),
+                        __builtin_amdgcn_alignbyte(a3, a2, sh), __builtin_amdgcn_alignbyte(a4, a3, sh)} &
+                  S.mask[len];
+  const uint32_t k = token_key(w, len);
+  uint32_t t = k & (kTab - 1);
+  for (uint32_t n = 0; n < kTab; ++n) {
+    const uint32_t tk = S.tkey[t];
+    if (!tk) break;
+    if (tk == k) {
+      const u32x4 q = S.qw[t];
+      const int32_t tq = S.tq[t];
+      if (q.x == w.x && q.y == w.y && q.z == w.z && q.w == w.w && (uint32_t)(tq >> 16) == len) {
+        atomicAdd(&S.cnt[wave][tq & 0xffff], 1u);
+        break;
+      }
+    }
+    t = (t + 1) & (kTab - 1);
   }
 }
 
@@ -155,104 +252,143 @@ __device__ __forceinline__ void load_sub(const uint8_t* stg, uint32_t lim, uint3
 // bytes from position 0 on are valid (later ones count as delimiters);
 // stg[kHead - 1] is the byte before position 0 when lb_ok (else position 0
 // starts a token if it is not a delimiter).  `lim` bytes from stg on lie in
-// the buffer.
-__device__ void scan_range(const WsArgs& A, Shared& S, uint32_t file, const uint8_t* stg,
+// the buffer.  Every work-item calls this; the counters and the table are
+// ready (a barrier came before).
+//
+// Bound by vector-ALU issue and LDS latency, about 4 us per 32 KiB of a
+// work-group.  (All lanes checking each token in full, over 32 KiB
+// sub-blocks between work-group barriers, took 27 us: the last 1 MiB chunk
+// of a pass then kept the launch 0.8 ms after the last read, and one file of
+// 500 KiB took 0.4 ms.)
+template <uint32_t WG>
+__device__ void scan_range(const WsArgs& A, Shared<WG>& S, uint32_t file, const uint8_t* stg,
                            uint32_t lim, uint32_t own_total, int64_t ext, bool lb_ok) {
-  const uint32_t wave = threadIdx.x >> 6;
+  constexpr uint32_t kWaves = WG / 64;
+  const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
   // staging bytes that hold data: the look-behind byte and positions < ext
   const uint32_t data = (uint32_t)min<int64_t>((int64_t)lim, (int64_t)kHead + max<int64_t>(ext, 0));
-  uint4 v[kPerLane];
-  if (own_total) load_sub(stg, lim, data, 0, v);
-  for (uint32_t sb0 = 0; sb0 < own_total; sb0 += kSB) {
-    // LDS buf[i] = staging[sb0 + i], i.e. chunk position sb0 + i - kHead
+  lptr_t<uint8_t> buf = lp(S.wb[wave].buf);
+  lptr_t<uint16_t> bits = lp(S.wb[wave].bits);
+  lptr_t<u64_any> bits64 = reinterpret_cast<lptr_t<u64_any>>(bits);
+  lptr_t<const u32_any> bits32 = reinterpret_cast<lptr_t<const u32_any>>(bits);
+  lptr_t<uint32_t> list = lp(S.wb[wave].list);
+  lptr_t<const uint32_t> filter = lp(S.filter);
+  u32x4 v[kPerLane];
+  uint32_t sb0 = wave * kSB;
+  if (sb0 < own_total) load_sub(stg, lim, data, sb0, v);
+  for (; sb0 < own_total; sb0 += kWaves * kSB) {
 #pragma unroll
     for (uint32_t k = 0; k < kPerLane; ++k) {
-      const uint32_t i = threadIdx.x + k * kWG;
-      if (i < kCopyVec) *reinterpret_cast<uint4*>(S.buf + i * 16) = v[k];
-    }
-    __syncthreads();
-    if (sb0 + kSB < own_total) load_sub(stg, lim, data, sb0 + kSB, v);  // in flight during the scan
-    const int64_t sb_ext = ext - (int64_t)sb0;                    // valid positions: p < sb_ext
-    const uint32_t own = min(kSB, own_total - sb0);               // tokens may start at p < own
-    const uint32_t p0 = threadIdx.x * kSeg;
-    if (p0 < own) {
-      // delimiter masks: bit i of dlo = position p0 + i, bit i of dhi =
-      // position p0 + 64 + i (read-ahead); bytes past the valid extent count
-      // as delimiters, and so does position 80 (a sentinel)
-      const uint32_t* bw = reinterpret_cast<const uint32_t*>(S.buf + kHead + p0);
-      uint64_t dlo = 0;
-      uint32_t dhi = 0;
-#pragma unroll
-      for (uint32_t d = 0; d < 16; ++d) dlo |= (uint64_t)delim4(bw[d]) << (4 * d);
-#pragma unroll
-      for (uint32_t d = 0; d < 4; ++d) dhi |= delim4(bw[16 + d]) << (4 * d);
-      const int64_t vlen = sb_ext - (int64_t)p0;  // valid bytes from p0 on
-      if (vlen < 64) dlo |= vlen <= 0 ? ~0ull : (~0ull << vlen);
-      if (vlen < 80) dhi |= vlen <= 64 ? 0xffffu : (0xffffu << (vlen - 64));
-      dhi |= 1u << 16;
-      uint32_t prev_delim;  // position p0 - 1
-      if (sb0 == 0 && p0 == 0) prev_delim = lb_ok ? (delim4(S.buf[kHead - 1]) & 1u) : 1u;
-      else if ((int64_t)p0 - 1 >= sb_ext) prev_delim = 1u;
-      else prev_delim = delim4(S.buf[kHead + p0 - 1]) & 1u;
-      const uint32_t own_n = min(kSeg, own - p0);
-      const uint64_t own_mask = own_n >= 64 ? ~0ull : ((1ull << own_n) - 1ull);
-      uint64_t starts = ~dlo & ((dlo << 1) | prev_delim) & own_mask;
-      while (starts) {
-        const uint32_t s = (uint32_t)__builtin_ctzll(starts);
-        starts &= starts - 1;
-        // first delimiter at or after s
-        const uint64_t after = s < 64 ? (dlo >> s) : 0ull;
-        uint32_t len;
-        if (after) len = (uint32_t)__builtin_ctzll(after);
-        else len = (64 - s) + (uint32_t)__builtin_ctz(dhi);
-        if (len > kOverlap) continue;
-        // the token's bytes, from aligned LDS words
-        const uint32_t bpos = kHead + p0 + s;
-        const uint32_t* aw = reinterpret_cast<const uint32_t*>(S.buf + (bpos & ~3u));
-        const uint32_t sh = bpos & 3u;
-        const uint32_t a0 = aw[0], a1 = aw[1], a2 = aw[2], a3 = aw[3], a4 = aw[4];
-        uint4 w = make_uint4(__builtin_amdgcn_alignbyte(a1, a0, sh),
-                             __builtin_amdgcn_alignbyte(a2, a1, sh),
-                             __builtin_amdgcn_alignbyte(a3, a2, sh),
-                             __builtin_amdgcn_alignbyte(a4, a3, sh));
-        w.x = mask_bytes(w.x, (int32_t)len);
-        w.y = mask_bytes(w.y, (int32_t)len - 4);
-        w.z = mask_bytes(w.z, (int32_t)len - 8);
-        w.w = mask_bytes(w.w, (int32_t)len - 12);
-        const uint32_t k = token_key(w, len);
-        uint32_t t = k & (kTab - 1);
-        for (uint32_t n = 0; n < kTab; ++n) {
-          const uint32_t tk = S.tkey[t];
-          if (!tk) break;
-          if (tk == k) {
-            const uint4 q = S.qw[t];
-            const int32_t tq = S.tq[t];
-            if (q.x == w.x && q.y == w.y && q.z == w.z && q.w == w.w &&
-                (uint32_t)(tq >> 16) == len) {
-              atomicAdd(&S.cnt[wave][tq & 0xffff], 1u);
-              break;
-            }
-          }
-          t = (t + 1) & (kTab - 1);
-        }
+      const uint32_t i = lane + k * 64;
+      if (i < kVecs) {
+        *reinterpret_cast<lptr_t<u32x4>>(buf + i * 16) = v[k];
+        bits[i + 3] = (uint16_t)delim16(v[k]);
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
+    if (sb0 + kWaves * kSB < own_total)  // in flight during the scan
+      load_sub(stg, lim, data, sb0 + kWaves * kSB, v);
+    const int64_t sb_ext = ext - (int64_t)sb0;       // valid positions: p < sb_ext
+    const uint32_t own = min(kSB, own_total - sb0);  // tokens may start at p < own
+    const uint32_t p0 = lane * kSeg;
+    // delimiter bits: bit i of dlo = position p0 + i; positions past the valid
+    // extent count as delimiters, in LDS too
+    uint64_t dlo = bits64[lane + 1];
+    if (sb_ext < kSB + kOverlap) {
+      const int64_t vlen = sb_ext - (int64_t)p0;  // valid bytes from p0 on
+      if (vlen < 64) {
+        dlo |= vlen <= 0 ? ~0ull : (~0ull << vlen);
+        bits64[lane + 1] = dlo;
+      }
+      if (lane == 63 && vlen < 80) bits[kVecs + 2] |= vlen <= 64 ? 0xffffu : (0xffffu << (vlen - 64));
+    }
+    uint32_t prev_delim = (uint32_t)(bits64[lane] >> 63);  // position p0 - 1
+    if (sb0 == 0 && p0 == 0) prev_delim = lb_ok ? prev_delim : 1u;
+    else if ((int64_t)p0 - 1 >= sb_ext) prev_delim = 1u;
+    uint64_t starts = ~dlo & ((dlo << 1) | prev_delim);
+    if (own < kSB) {
+      const uint32_t own_n = own > p0 ? min(kSeg, own - p0) : 0u;
+      starts &= own_n >= 64 ? ~0ull : ((1ull << own_n) - 1ull);
+    }
+    // the positions of all starts, packed in order (lanes hold 0 to 32 each)
+    const uint32_t mine = (uint32_t)__popcll(starts);
+    const uint32_t upto = wave_scan(mine);
+    const uint32_t total = __builtin_amdgcn_readlane(upto, 63);
+    lptr_t<uint16_t> at = lp(S.wb[wave].starts) + (upto - mine);
+    while (__ballot(starts != 0)) {
+      if (starts) {
+        *at++ = (uint16_t)(p0 + (uint32_t)__builtin_ctzll(starts));
+        starts &= starts - 1;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    uint32_t n = 0;  // listed tokens (the same in every lane)
+    for (uint32_t i = 0; i < total; i += 128) {
+      // two tokens per lane at a time: their LDS reads overlap
+      bool pass[2];
+      uint32_t pos[2], w0[2], w1[2], len[2], f[2], fw[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        pass[u] = i + 64 * u + lane < total;
+        pos[u] = pass[u] ? lp(S.wb[wave].starts)[i + 64 * u + lane] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t k = (pos[u] + 64) >> 5;
+        w0[u] = bits32[k];
+        w1[u] = bits32[k + 1];
+        f[u] = text4(buf, kHead + pos[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        // the first delimiter after the start, 17 for more than 16 bytes
+        const uint32_t win = __builtin_amdgcn_alignbit(w1[u], w0[u], pos[u] & 31u) | (1u << 17);
+        len[u] = (uint32_t)__builtin_ctz(win);
+        pass[u] = pass[u] && len[u] <= kOverlap;
+        f[u] = filter_bit(f[u], len[u]);
+        fw[u] = filter[f[u] >> 5];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        pass[u] = pass[u] && ((fw[u] >> (f[u] & 31u)) & 1u);
+        const uint64_t m = __ballot(pass[u]);
+        if (pass[u])
+          list[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+              (kHead + pos[u]) | (len[u] << 16);
+        n += (uint32_t)__popcll(m);
+      }
+      while (n >= 64) {
+        __builtin_amdgcn_wave_barrier();
+        n -= 64;
+        const uint32_t e = list[n + lane];
+        count_token(S, wave, buf, e & 0xffffu, e >> 16);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (n) {
+      const uint32_t e = lane < n ? list[lane] : 0u;
+      count_token(S, wave, buf, e & 0xffffu, e >> 16);
+    }
+    __builtin_amdgcn_wave_barrier();
   }
+  __syncthreads();
   // flush this chunk's counts
   for (uint32_t q = threadIdx.x; q < A.nq; q += blockDim.x) {
-    uint32_t v = 0;
+    uint32_t c = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < kWG / 64; ++w) {
-      v += S.cnt[w][q];
+    for (uint32_t w = 0; w < kWaves; ++w) {
+      c += S.cnt[w][q];
       S.cnt[w][q] = 0;
     }
-    if (v) atomicAdd(&A.counts[(uint64_t)file * A.nq + q], v);
+    if (c) atomicAdd(&A.counts[(uint64_t)file * A.nq + q], c);
   }
   __syncthreads();
 }
 
-__device__ void scan_chunk(const WsArgs& A, Shared& S, uint32_t ci, uint64_t slot, int64_t ret) {
+template <uint32_t WG>
+__device__ void scan_chunk(const WsArgs& A, Shared<WG>& S, uint32_t ci, uint64_t slot, int64_t ret) {
   const gsys_chunk ch = A.chunks[ci];
   const uint32_t lb = ch.off > 0 ? 1u : 0u;
   // bytes available at chunk positions >= 0 (chunk + read-ahead, EOF-bounded)
@@ -269,7 +405,8 @@ __device__ void scan_chunk(const WsArgs& A, Shared& S, uint32_t ci, uint64_t slo
 // lets the other work-items of thread 0's wavefront pass the barrier below
 // before thread 0 has taken the item, read a stale S.next, and never leave
 // the loop.
-__device__ __forceinline__ uint32_t grab(const WsArgs& A, Shared& S) {
+template <uint32_t WG>
+__device__ __forceinline__ uint32_t grab(const WsArgs& A, Shared<WG>& S) {
   __syncthreads();
   if (threadIdx.x == 0) S.next = atomicAdd(A.work, 1u);
   __syncthreads();
@@ -283,13 +420,14 @@ __device__ __forceinline__ uint32_t grab(const WsArgs& A, Shared& S) {
 // chunk w mod n_chunks of pass w / n_chunks: with several passes the
 // work-groups go from one pass to the next without draining, and each pass
 // adds its counts.
-__global__ __launch_bounds__(kWG) void wordscan_persistent(WsArgs A) {
-  __shared__ Shared S;
-  build_table(A, S);
+template <uint32_t WG>
+__global__ __launch_bounds__(WG) void wordscan_persistent(WsArgs A) {
+  __shared__ Shared<WG> S;
   const uint32_t total = A.n_chunks * A.passes;
   uint32_t cur = grab(A, S);
   if (cur >= total) return;
   uint32_t bi = 0;
+  build_table(A, S);  // the barriers of the calls below end it
   Ticket tk = issue_chunk(A, cur % A.n_chunks, (uint64_t)blockIdx.x * 2 + bi);
   for (;;) {
     const uint32_t nxt = grab(A, S);
@@ -307,8 +445,9 @@ __global__ __launch_bounds__(kWG) void wordscan_persistent(WsArgs A) {
 
 // Plain form: one work-group per chunk, blocking relaxed work-group call
 // (the paper's wordcount setting: work-group granularity, blocking, weak).
-__global__ __launch_bounds__(kWG) void wordscan_plain(WsArgs A) {
-  __shared__ Shared S;
+template <uint32_t WG>
+__global__ __launch_bounds__(WG) void wordscan_plain(WsArgs A) {
+  __shared__ Shared<WG> S;
   build_table(A, S);
   const uint32_t ci = blockIdx.x;
   if (ci >= A.n_chunks) return;
@@ -316,6 +455,8 @@ __global__ __launch_bounds__(kWG) void wordscan_plain(WsArgs A) {
   const uint32_t lb = ch.off > 0 ? 1u : 0u;
   const uint64_t dst = A.staging + (uint64_t)ci * A.cbuf + kHead - lb;
   Args6 a{{(uint64_t)(int64_t)ch.fd, dst, (uint64_t)ch.len + kOverlap + lb, ch.off - lb, 0, 0}};
+  // a consumer call has no barrier before it: the table is built while the
+  // first wavefront waits
   const int64_t r = call_wg<O::Relaxed, B::Blocking>(A.c, GSYS_NR_PREAD64, 0, a);
   scan_chunk(A, S, ci, ci, r);
 }
@@ -335,6 +476,7 @@ __global__ __launch_bounds__(kWG) void wordscan_plain(WsArgs A) {
 // at kOpenHead - 17, each piece's data on a fresh 64-byte line.
 
 constexpr uint32_t kOpenHead = 64;
+constexpr uint32_t kOpenTail = (32u << 10) + 48;  // room past the piece
 constexpr uint32_t kCarry = kOverlap;  // deferred bytes
 
 struct WoArgs {
@@ -359,7 +501,8 @@ __device__ __forceinline__ void progress(const WoArgs& A, uint32_t f, uint32_t p
   st_sys(p, ((uint64_t)(f + 1) << 32) | phase);
 }
 
-__device__ void open_and_scan(const WoArgs& A, Shared& S, uint32_t f) {
+template <uint32_t WG>
+__device__ void open_and_scan(const WoArgs& A, Shared<WG>& S, uint32_t f) {
   const gsys_dev_ctx& c = A.w.c;
   const uint64_t base = A.w.staging + (uint64_t)blockIdx.x * 2 * A.w.cbuf;
   progress(A, f, kPhOpen, 0, 0);
@@ -423,22 +566,25 @@ __device__ void open_and_scan(const WoArgs& A, Shared& S, uint32_t f) {
   if (threadIdx.x == 0) A.file_ret[f] = err ? err : (rc < 0 ? rc : total);
 }
 
-__global__ __launch_bounds__(kWG) void wordopen_persistent(WoArgs A) {
-  __shared__ Shared S;
-  build_table(A.w, S);
+template <uint32_t WG>
+__global__ __launch_bounds__(WG) void wordopen_persistent(WoArgs A) {
+  __shared__ Shared<WG> S;
   uint32_t last = ~0u;
-  for (;;) {
-    // grab() opens with a barrier: the thread-0-only result store that ends
-    // open_and_scan never shares a region with the next grab's atomic
-    const uint32_t f = grab(A.w, S);
-    if (f >= A.nfiles) break;
+  uint32_t f = grab(A.w, S);
+  if (f < A.nfiles) build_table(A.w, S);  // while the first openat is served
+  while (f < A.nfiles) {
     open_and_scan(A, S, f);
     last = f;
+    // grab() opens with a barrier: the thread-0-only result store that ends
+    // open_and_scan never shares a region with the next grab's atomic
+    f = grab(A.w, S);
   }
   progress(A, last, kPhDone, 0, 0);
 }
 
-__global__ void zero_u32(uint32_t* p, uint64_t n) {
+// Clear the counts and the work counter before a scan.
+__global__ void zero_counts(uint32_t* p, uint64_t n, uint32_t* work) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *work = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x)
     p[i] = 0;
@@ -477,40 +623,44 @@ int gsys_wordscan(gsys_ctx* ctx, uint64_t chunks, uint32_t n_chunks, uint32_t ch
   if (form != GSYS_PLAIN && form != GSYS_PERSISTENT && form != GSYS_GRAPH) return -EINVAL;
   // zero the counts and the work counter, then scan
   uint64_t ncount = (uint64_t)nfiles * nq;
-  uint64_t nwork = 2;
   uint32_t* counts32 = (uint32_t*)counts;
   uint32_t* work32 = (uint32_t*)A.work;
-  void* zc_args[] = {&counts32, &ncount};
-  void* zw_args[] = {&work32, &nwork};
+  void* z_args[] = {&counts32, &ncount, &work32};
   void* args[] = {&A};
-  const dim3 zc_grid((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((ncount + 255) / 256, 4096)));
-  gsys_internal::KLaunch k[3] = {{(const void*)zero_u32, zc_grid, dim3(256), 0, zc_args},
-                                 {(const void*)zero_u32, dim3(1), dim3(64), 0, zw_args},
-                                 {nullptr, dim3(1), dim3(kWG), 0, args}};
+  const dim3 z_grid((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((ncount + 255) / 256, 4096)));
+  gsys_internal::KLaunch k[2] = {{(const void*)zero_counts, z_grid, dim3(256), 0, z_args},
+                                 {nullptr, dim3(1), dim3(kNarrow), 0, args}};
   if (form == GSYS_PLAIN) {
     if (n_chunks && staging_bytes < (uint64_t)cbuf * n_chunks) return -EINVAL;
-    k[2].kernel = (const void*)wordscan_plain;
-    k[2].grid = dim3(n_chunks);
+    const bool wide = n_chunks <= gsys_internal::cu_count(ctx);
+    k[1].kernel = wide ? (const void*)wordscan_plain<kWide> : (const void*)wordscan_plain<kNarrow>;
+    k[1].block = dim3(wide ? kWide : kNarrow);
+    k[1].grid = dim3(n_chunks);
   } else {
     if (n_chunks && staging_bytes < per_wg) return -EINVAL;
-    uint32_t grid = gsys_internal::resident_grid(ctx, (const void*)wordscan_persistent, kWG, 0);
+    const uint64_t items = (uint64_t)n_chunks * passes;
+    // as many work-groups as are resident, have staging and have a chunk
+    const bool wide = items <= staging_bytes / per_wg;
+    const void* kp = wide ? (const void*)wordscan_persistent<kWide>
+                          : (const void*)wordscan_persistent<kNarrow>;
+    const uint32_t block = wide ? kWide : kNarrow;
+    uint32_t grid = gsys_internal::resident_grid(ctx, kp, block, 0);
     if (!grid) return -ENODEV;
-    grid = (uint32_t)std::min<uint64_t>(
-        {(uint64_t)grid, staging_bytes / per_wg, (uint64_t)n_chunks * passes});
+    grid = (uint32_t)std::min<uint64_t>({(uint64_t)grid, staging_bytes / per_wg, items});
     const uint32_t req = gsys_internal::persistent_grid_override(ctx);
     if (req && req < grid) grid = req;
-    k[2].kernel = (const void*)wordscan_persistent;
-    k[2].grid = dim3(grid);
+    k[1].kernel = kp;
+    k[1].block = dim3(block);
+    k[1].grid = dim3(grid);
   }
   if (form == GSYS_GRAPH && n_chunks) {
-    // one graph per shape: both fills and the scan, replayed with this
-    // call's arguments
-    const uint64_t key = gsys_internal::hash_words(
-        {0x3C5ull, zc_grid.x, k[2].grid.x});
-    return gsys_internal::launch_graph(ctx, key, k, 3, s);
+    // one graph per shape: the fill and the scan, replayed with this call's
+    // arguments
+    const uint64_t key = gsys_internal::hash_words({0x3C5ull, z_grid.x, k[1].grid.x, k[1].block.x});
+    return gsys_internal::launch_graph(ctx, key, k, 2, s);
   }
-  for (uint32_t i = 0; i < 3; ++i) {
-    if (i == 2 && !n_chunks) break;
+  for (uint32_t i = 0; i < 2; ++i) {
+    if (i == 1 && !n_chunks) break;
     if (int e = gsys_internal::launch(ctx, k[i].kernel, k[i].grid.x, k[i].block.x, 0, k[i].args, s))
       return e;
   }
@@ -518,7 +668,7 @@ int gsys_wordscan(gsys_ctx* ctx, uint64_t chunks, uint32_t n_chunks, uint32_t ch
 }
 
 uint64_t gsys_wordcount_open_buffer_bytes(uint32_t chunk) {
-  return ((uint64_t)kOpenHead + chunk + kCopy + 15) & ~15ull;
+  return ((uint64_t)kOpenHead + chunk + kOpenTail + 15) & ~15ull;
 }
 
 int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfiles,
@@ -560,11 +710,14 @@ int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfile
   A.dirfd = dirfd;
   const uint64_t ncount = (uint64_t)nfiles * nq;
   if (gsys_internal::no_device(ctx)) return -ENODEV;
-  hipLaunchKernelGGL(zero_u32, dim3((uint32_t)std::min<uint64_t>((ncount + 255) / 256, 4096)),
-                     dim3(256), 0, s, (uint32_t*)counts, ncount);
-  hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, s, (uint32_t*)A.w.work, (uint64_t)2);
+  hipLaunchKernelGGL(zero_counts, dim3((uint32_t)std::min<uint64_t>((ncount + 255) / 256, 4096)),
+                     dim3(256), 0, s, (uint32_t*)counts, ncount, (uint32_t*)A.w.work);
   if (hipGetLastError() != hipSuccess) return -ENODEV;
-  uint32_t grid = gsys_internal::resident_grid(ctx, (const void*)wordopen_persistent, kWG, 0);
+  const bool wide = nfiles <= staging_bytes / per_wg;
+  const void* kp = wide ? (const void*)wordopen_persistent<kWide>
+                        : (const void*)wordopen_persistent<kNarrow>;
+  const uint32_t block = wide ? kWide : kNarrow;
+  uint32_t grid = gsys_internal::resident_grid(ctx, kp, block, 0);
   if (!grid) return -ENODEV;
   grid = (uint32_t)std::min<uint64_t>({(uint64_t)grid, staging_bytes / per_wg, (uint64_t)nfiles});
   const uint32_t req = gsys_internal::persistent_grid_override(ctx);
@@ -572,5 +725,5 @@ int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfile
   if (progress && progress_groups < grid) grid = progress_groups;  // one record per work-group
   A.progress = progress;
   void* args[] = {&A};
-  return gsys_internal::launch(ctx, (const void*)wordopen_persistent, grid, kWG, 0, args, s);
+  return gsys_internal::launch(ctx, kp, grid, block, 0, args, s);
 }
