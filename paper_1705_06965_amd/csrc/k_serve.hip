@@ -278,7 +278,9 @@ __device__ void run_job(const SvArgs& A, uint32_t j, uint8_t* lds, uint64_t stg0
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kWG) void serve_persistent(SvArgs A) {
+// Two wavefronts per SIMD keep the kernel to 256 registers: the runtime's
+// occupancy query has failed for it with 264 (hipErrorUnknown).
+__global__ __launch_bounds__(kWG, 2) void serve_persistent(SvArgs A) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int s_job;
   __shared__ unsigned int s_task;
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(kWG) void serve_persistent(SvArgs A) {
   }
 }
 
-__global__ __launch_bounds__(kWG) void serve_one(SvArgs A, uint32_t j) {
+__global__ __launch_bounds__(kWG, 2) void serve_one(SvArgs A, uint32_t j) {
   extern __shared__ __align__(16) uint8_t lds[];
   run_job(A, j, lds, A.staging, A.staging + kPiece);
 }
