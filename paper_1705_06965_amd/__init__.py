@@ -321,6 +321,35 @@ class Context:
                      "gsys_fnv4k")
 
 
+class Readback:
+    """A driver's result tensors and their pinned host copies (made on first
+    use and kept)."""
+
+    def __init__(self, *tensors):
+        self.src = tensors
+        self.dst = None
+        self.queued = False
+
+    def enqueue(self, stream=None):
+        """Queue the copies behind the launch just made on `stream`, if that is
+        the stream torch's copies go to (otherwise read() makes them)."""
+        import torch
+        if self.dst is None:
+            self.dst = [torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for t in self.src]
+        self.queued = _stream(stream) == torch.cuda.current_stream().cuda_stream
+        if self.queued:
+            for d, t in zip(self.dst, self.src):
+                d.copy_(t, non_blocking=True)
+
+    def read(self):
+        """The results as numpy arrays of their own, once the device is
+        synchronised."""
+        if not self.queued:
+            for d, t in zip(self.dst, self.src):
+                d.copy_(t)
+        return [d.numpy().copy() for d in self.dst]
+
+
 def exported_symbols():
     """Names of the C functions declared in include/*.h."""
     import re

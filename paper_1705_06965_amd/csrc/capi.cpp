@@ -11,6 +11,8 @@
 #include <time.h>
 #include <unistd.h>
 
+#include <immintrin.h>
+
 #include <hip/hip_runtime.h>
 #include <hsa/amd_hsa_signal.h>
 #include <hsa/hsa.h>
@@ -100,7 +102,7 @@ struct gsys_ctx {
   gsys_slot* ring = nullptr;       // host view
   gsys_comp* comp = nullptr;       // host view
   // host-coherent page: [0] retired_lo, [32] the ticket counter of NO_DEVICE
-  // contexts, [64] sleeping pollers, [96..97] serving control words; each
+  // contexts, [40] the device's ticket counter as last read, [64] sleeping pollers, [96..97] serving control words; each
   // group on its own 256-byte line
   uint64_t* host_words = nullptr;
   gsys_slot* ring_dev = nullptr;
@@ -112,6 +114,7 @@ struct gsys_ctx {
   gsys_host::Pool* pool = nullptr;
   hipStream_t aux = nullptr;
   std::mutex mu;
+  std::mutex drain_mu;             // host_words[40] while claimed_tickets() fills it
   std::map<void*, std::pair<uint64_t, uint32_t>> host_allocs;  // host ptr -> (bytes, id)
   uint8_t* arena = nullptr;
   uint64_t arena_bytes = 0;
@@ -184,11 +187,25 @@ void host_coherent_free(gsys_ctx* c, void* host) {
 
 uint64_t claimed_tickets(gsys_ctx* c) {
   if (c->no_device) return __atomic_load_n(&c->host_words[32], __ATOMIC_ACQUIRE);
-  unsigned long long v = 0;
+  // A one-thread kernel stores the counter into the context's pinned page and
+  // the host watches that word: 9 us, against 21 for a copy to pageable memory
+  // and a stream synchronisation, 13 for one to pinned memory.
+  constexpr uint64_t kUnset = ~0ull;  // no ticket gets that far
+  std::lock_guard<std::mutex> g(c->drain_mu);
   hipSetDevice(c->device);
-  if (hipMemcpyAsync(&v, c->dev_words, sizeof v, hipMemcpyDeviceToHost, c->aux) != hipSuccess)
+  __atomic_store_n(&c->host_words[40], kUnset, __ATOMIC_RELEASE);
+  if (!gsys_internal::launch_read_tail ||
+      !gsys_internal::launch_read_tail(c->dev_words, (uint64_t)(c->retired_lo_dev + 40), c->aux))
     return 0;
-  hipStreamSynchronize(c->aux);
+  uint64_t v;
+  for (uint32_t spins = 1; (v = __atomic_load_n(&c->host_words[40], __ATOMIC_ACQUIRE)) == kUnset; ++spins) {
+    _mm_pause();
+    // a kernel that ended without storing (a failed device) ends the wait too
+    if ((spins & 0xffff) == 0 && hipStreamQuery(c->aux) != hipErrorNotReady) {
+      v = __atomic_load_n(&c->host_words[40], __ATOMIC_ACQUIRE);
+      return v == kUnset ? 0 : v;
+    }
+  }
   return v;
 }
 

@@ -21,7 +21,16 @@ __global__ void clear_sites(unsigned long long* p, uint32_t n) {
   if (i < n) p[i] = 0;
 }
 
+__global__ void read_tail(const unsigned long long* tail, uint64_t* out) {
+  gsys::st_sys_rel(out, __hip_atomic_load(tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 }  // namespace gsys_ln
+
+bool gsys_internal::launch_read_tail(const unsigned long long* tail, uint64_t out, hipStream_t s) {
+  hipLaunchKernelGGL(gsys_ln::read_tail, dim3(1), dim3(1), 0, s, tail, (uint64_t*)out);
+  return hipGetLastError() == hipSuccess;
+}
 
 int gsys_launch(gsys_ctx* c, const gsys_launch_desc* d, void* stream) {
   if (!c || !d || !d->kernel) return -EINVAL;

@@ -35,6 +35,10 @@ int device_of(gsys_ctx* ctx);
 // build of the context and pool (the sanitizer test driver) has no kernels,
 // and there the symbol is null.
 int serve_scratch_setup(int device) __attribute__((weak));
+// Store the ticket counter `tail` (device memory) to the host-coherent word
+// whose device address is `out`, on stream s.  Weak for the same reason.
+bool launch_read_tail(const unsigned long long* tail, uint64_t out, hipStream_t s)
+    __attribute__((weak));
 // Device wall-clock ticks per millisecond.
 uint64_t ticks_per_ms(gsys_ctx* ctx);
 int launch(gsys_ctx* ctx, const void* kernel, uint32_t grid, uint32_t block, uint32_t lds,

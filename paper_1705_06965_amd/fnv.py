@@ -7,7 +7,7 @@ import os
 
 import numpy as np
 
-from . import (Context, FD_READ, PLAIN, PERSISTENT, GRAPH, check, lib, cell_code,
+from . import (Context, FD_READ, PLAIN, PERSISTENT, GRAPH, Readback, check, lib, cell_code,
                _stream)
 
 
@@ -28,8 +28,9 @@ class FnvRunner:
         self.lists = ctx.host_alloc(max(16, self.n * 16))
         offs = np.ascontiguousarray(offsets, dtype=np.uint64)
         self.offsets = torch.from_numpy(offs.view(np.int64)).to(device)
-        self.out_fnv = torch.zeros(max(1, self.n), dtype=torch.int64, device=device)
-        self.out_ret = torch.zeros(max(1, self.n), dtype=torch.int64, device=device)
+        self.out = torch.zeros((2, max(1, self.n)), dtype=torch.int64, device=device)
+        self.out_fnv, self.out_ret = self.out[0], self.out[1]
+        self.back = Readback(self.out)
 
     def launch(self, cell: int = 0, form: int = PLAIN, stream=None):
         return check(lib.gsys_fnv4k(self.ctx.h, self.fd, self.offsets.data_ptr(), self.n,
@@ -39,15 +40,16 @@ class FnvRunner:
                                     self.wg_size, _stream(stream)), "gsys_fnv4k")
 
     def run(self, g="WI", o="strong", b="block", form=PLAIN, stream=None):
-        """Launch, wait for the GPU and drain the host pool."""
-        self.out_fnv.zero_()
-        self.out_ret.fill_(-12345)
+        """Launch, wait for the GPU and drain the host pool (every form stores
+        both results of every item)."""
         self.launch(cell_code(g, o, b), form, stream)
+        self.back.enqueue(stream)
         self.torch.cuda.synchronize()
         rc = self.ctx.wait(60_000_000_000)
         if rc:
             raise RuntimeError("drain failed: %d" % rc)
-        return self.result()
+        f, r = self.back.read()[0]
+        return f.view(np.uint64)[:self.n], r[:self.n]
 
     def result(self):
         f = self.out_fnv.cpu().numpy().view(np.uint64)[:self.n].copy()

@@ -8,7 +8,7 @@ import os
 
 import numpy as np
 
-from . import Context, FD_WRITE, check, lib, cell_code, _stream
+from . import Context, FD_WRITE, Readback, check, lib, cell_code, _stream
 
 BLOCK = 8192
 WG_CELLS = [("WG", "strong", "block"), ("WG", "strong", "nonblock"),
@@ -34,6 +34,7 @@ class PermuteRunner:
         self.data = torch.from_numpy(d.view(np.int64)).to(device)
         self.staging = ctx.host_alloc(max(1, self.n) * BLOCK)
         self.out_ret = torch.zeros(max(1, self.n), dtype=torch.int64, device=device)
+        self.back = Readback(self.out_ret)
 
     def launch(self, iters: int, cell: int, stream=None):
         return check(lib.gsys_permute(self.ctx.h, self.fd, self.data.data_ptr(),
@@ -45,13 +46,13 @@ class PermuteRunner:
     def run(self, iters: int, g="WG", o="strong", b="block", stream=None):
         """Launch, wait for the GPU, drain the host pool; per-block results
         (pwrite's return value for blocking cells)."""
-        self.out_ret.fill_(-12345)
         self.launch(iters, cell_code(g, o, b), stream)
+        self.back.enqueue(stream)
         self.torch.cuda.synchronize()
         rc = self.ctx.wait(60_000_000_000)
         if rc:
             raise RuntimeError("drain failed: %d" % rc)
-        return self.out_ret.cpu().numpy()[:self.n].copy()
+        return self.back.read()[0][:self.n]
 
     def file_bytes(self) -> np.ndarray:
         return np.fromfile(self.path, dtype=np.uint8)[self.file_off:self.file_off + self.n * BLOCK]

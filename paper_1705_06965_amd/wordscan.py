@@ -6,7 +6,7 @@ import os
 
 import numpy as np
 
-from . import FD_READ, PERSISTENT, PLAIN, check, lib, _stream
+from . import FD_READ, PERSISTENT, PLAIN, Readback, check, lib, _stream
 
 CHUNK_DTYPE = np.dtype([("fd", "<i4"), ("file", "<u4"), ("off", "<u8"), ("len", "<u4"),
                         ("pad", "<u4")])
@@ -57,6 +57,7 @@ class WordScanRunner:
         self.queries = torch.from_numpy(q).to(device)
         self.qlens = torch.from_numpy(ql.view(np.int32)).to(device)
         self.counts = torch.zeros(max(1, self.nfiles * self.nq), dtype=torch.int32, device=device)
+        self.back = Readback(self.counts)
         if not persistent_buffers:
             persistent_buffers = int(os.environ.get("GSYS_WS_BUFFERS", "128"))
         self.persistent_bytes = staging_bytes(chunk_max, min(persistent_buffers,
@@ -82,11 +83,15 @@ class WordScanRunner:
 
     def run(self, form=PERSISTENT, stream=None, passes: int = 1):
         self.launch(form, stream, passes)
+        self.back.enqueue(stream)
         self.torch.cuda.synchronize()
         rc = self.ctx.wait(60_000_000_000)
         if rc:
             raise RuntimeError("drain failed: %d" % rc)
-        return self.result()
+        return self._counts(self.back.read()[0])
+
+    def _counts(self, c):
+        return c.view(np.uint32)[:self.nfiles * self.nq].reshape(self.nfiles, self.nq)
 
     def result(self):
         return self.counts.cpu().numpy().view(np.uint32)[:self.nfiles * self.nq] \
@@ -156,6 +161,7 @@ class WordOpenRunner:
         self.qlens = torch.from_numpy(ql.view(np.int32)).to(device)
         self.counts = torch.zeros(max(1, self.nfiles * self.nq), dtype=torch.int32, device=device)
         self.file_ret = torch.zeros(max(1, self.nfiles), dtype=torch.int64, device=device)
+        self.back = Readback(self.counts, self.file_ret)
         self.groups = max(1, min(groups, self.nfiles))
         self.staging_bytes = 2 * open_buffer_bytes(chunk) * self.groups
         self.staging = ctx.host_alloc(self.staging_bytes)
@@ -184,12 +190,11 @@ class WordOpenRunner:
         launch is awaited with a host-side deadline; past it the work-groups'
         progress records are raised in the error."""
         import time
-        self.file_ret.fill_(-12345)
         self.progress.array[:16 * self.groups] = 0
-        ev = self.torch.cuda.Event()
         self.launch(stream)
-        ev.record()
         if timeout_s:
+            ev = self.torch.cuda.Event()
+            ev.record()
             t0 = time.monotonic()
             while not ev.query():
                 if time.monotonic() - t0 > timeout_s:
@@ -197,11 +202,14 @@ class WordOpenRunner:
                                        "progress (file, phase, piece, ticket) per work-group: %r"
                                        % (timeout_s, self.progress_records()))
                 time.sleep(0.002)
+        self.back.enqueue(stream)
         self.torch.cuda.synchronize()
         rc = self.ctx.wait(60_000_000_000)
         if rc:
             raise RuntimeError("drain failed: %d" % rc)
-        return self.result()
+        c, ret = self.back.read()
+        return c.view(np.uint32)[:self.nfiles * self.nq].reshape(self.nfiles, self.nq), \
+            ret[:self.nfiles]
 
     def result(self):
         c = self.counts.cpu().numpy().view(np.uint32)[:self.nfiles * self.nq] \
