@@ -310,7 +310,8 @@ const char *gsys_strerror(int code);
  *             64 groups keep enough reads in flight.
  *   wg_size   work-items per work-group: 64, 128, 256, 512 or 1024.  A launch
  *             may give its work-groups further wavefronts that make no calls
- *             and help to hash (items of more than 512 bytes).
+ *             and help to hash, and may spread work-item calls over more and
+ *             smaller work-groups (items of more than 512 bytes).
  * item_bytes must be a multiple of 64 and at most 1 MiB; n_items % wg_size
  * need not be 0 (the tail work-group is partial).  n_items == 0 returns 0 at
  * once, launching nothing.
