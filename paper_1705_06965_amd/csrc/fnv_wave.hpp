@@ -148,7 +148,8 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
 // a wavefront (27 cycles per byte and lane; the serial chain takes 32), but a
 // 4 KiB item takes half a step instead of the chain's 61 us.  Measured: 50,000
 // items of 4 KiB in HBM 110 -> 61 us (3.4 TB/s), 180 of 1 MiB 15.4 -> 0.27 ms,
-// 64 of 4 KiB read and hashed by one work-group 99 -> 38 us.
+// a kernel that reads 64 of 4 KiB by one list call and hashes them in one
+// work-group of eight wavefronts 85 -> 42 us.
 
 constexpr uint64_t kFnvPrime = 0x100000001b3ull;
 constexpr uint64_t kFnvBasis = 0xcbf29ce484222325ull;

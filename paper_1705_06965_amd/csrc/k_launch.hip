@@ -28,8 +28,9 @@ __global__ void read_tail(const unsigned long long* tail, uint64_t* out) {
 }  // namespace gsys_ln
 
 bool gsys_internal::launch_read_tail(const unsigned long long* tail, uint64_t out, hipStream_t s) {
-  hipLaunchKernelGGL(gsys_ln::read_tail, dim3(1), dim3(1), 0, s, tail, (uint64_t*)out);
-  return hipGetLastError() == hipSuccess;
+  // (the launch's own status: hipGetLastError may hold an earlier error of the caller's)
+  void* args[] = {&tail, &out};
+  return hipLaunchKernel((const void*)gsys_ln::read_tail, dim3(1), dim3(1), args, 0, s) == hipSuccess;
 }
 
 int gsys_launch(gsys_ctx* c, const gsys_launch_desc* d, void* stream) {

@@ -96,3 +96,49 @@ def test_helpers_and_short_lists(gs, tmpdata, n, item, wg, form, cell):
     f, ret = r.run(*cell, form={"plain": g.PLAIN, "persistent": g.PERSISTENT, "graph": g.GRAPH}[form])
     r.close()
     assert (ret == want_ret).all() and (f == want).all()
+
+
+def test_drain_reads_the_counter_after_an_error_of_the_callers(gs, tmpdata):
+    """A runtime error that the caller has not cleared (a device that does not
+    exist) is not the drain's: the claimed count is the device's."""
+    import ctypes
+    import os
+    from paper_1705_06965_amd.fnv import FnvRunner
+    g, ctx = gs
+    path = os.path.join(tmpdata, "drain.bin")
+    np.zeros(4096, dtype=np.uint8).tofile(path)
+    r = FnvRunner(ctx, path, np.zeros(3, dtype=np.uint64), 64, wg_size=64)
+    r.run()
+    r.close()
+    with open("/proc/self/maps") as f:
+        so = next(l.split()[-1] for l in f if "libamdhip64" in l)
+    hip = ctypes.CDLL(so)
+    before = ctx.stats()["claimed"]
+    assert before >= 3
+    try:
+        assert hip.hipSetDevice(1 << 20) != 0
+        assert ctx.stats()["claimed"] == before
+    finally:
+        hip.hipGetLastError()
+
+
+@pytest.mark.parametrize("wg", [64, 1024])
+@pytest.mark.parametrize("over", [0, 1])
+def test_spread_work_groups_at_the_last_size(gs, tmpdata, wg, over):
+    """The most items that work-groups of 16 spread over all compute units
+    take, and one more."""
+    import os
+    import torch
+    from paper_1705_06965_amd.fnv import FnvRunner
+    g, ctx = gs
+    n = 16 * torch.cuda.get_device_properties(0).multi_processor_count + over
+    rng = np.random.default_rng(n)
+    path = os.path.join(tmpdata, "spread.bin")
+    rng.integers(0, 256, 100000, dtype=np.uint8).tofile(path)
+    offs = rng.integers(0, 100100, n).astype(np.uint64)
+    want, want_ret = oracle.pread_fnv(path, offs, 4096)
+    r = FnvRunner(ctx, path, offs, 4096, wg_size=wg)
+    print("spread", n, wg, flush=True)
+    f, ret = r.run("WI", "strong", "block")
+    r.close()
+    assert (ret == want_ret).all() and (f == want).all()
