@@ -144,10 +144,10 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
 // 512 bytes.  Bytes past an item's end are zeros: a zero byte multiplies h by
 // p, which the inverse of p undoes.
 //
-// Bound by vector-ALU issue: 821 instructions and 16 MFMAs per 8 KiB step of
-// a wavefront (27 cycles per byte and lane; the serial chain takes 32), but a
+// Bound by vector-ALU issue: 781 instructions and 16 MFMAs per 8 KiB step of
+// a wavefront (26 cycles per byte and lane; the serial chain takes 32), but a
 // 4 KiB item takes half a step instead of the chain's 61 us.  Measured: 50,000
-// items of 4 KiB in HBM 110 -> 61 us (3.4 TB/s), 180 of 1 MiB 15.4 -> 0.27 ms,
+// items of 4 KiB in HBM 106 -> 59 us (3.5 TB/s), 180 of 1 MiB 15.4 -> 0.27 ms,
 // a kernel that reads 64 of 4 KiB by one list call and hashes them in one
 // work-group of eight wavefronts 85 -> 42 us.
 
@@ -219,7 +219,14 @@ __device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) {
 }
 
 // 8 x 8 bit transpose in every byte column: bit j of byte c of a[r] <-> bit r
-// of byte c of a[j].
+// of byte c of a[j].  A step exchanges the fields m of one row with the fields
+// ~m of the row s below; the lower row is left rotated by s, so that one
+// rotation serves both rows.  Rows of a pair always have the same rotation;
+// row r ends with r, which one rotation each takes out: 43 instructions, 48
+// with two shifts a pair (50,000 items of 4 KiB in HBM 60.8 -> 59.2 us).
+__device__ __forceinline__ uint32_t rotl(uint32_t v, uint32_t s) {
+  return __builtin_amdgcn_alignbit(v, v, (32 - s) & 31);
+}
 __device__ __forceinline__ void transpose_bits(uint32_t (&a)[8]) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -227,11 +234,15 @@ __device__ __forceinline__ void transpose_bits(uint32_t (&a)[8]) {
 #pragma unroll
     for (uint32_t r = 0; r < 8; ++r)
       if (!(r & s)) {
-        const uint32_t lo = a[r], hi = a[r + s];
-        a[r] = bfi(m, lo, hi << s);
-        a[r + s] = bfi(m, lo >> s, hi);
+        const uint32_t rot = r & (s - 1u);  // of both rows
+        const uint32_t mr = rot ? (m << rot) | (m >> (32 - rot)) : m;
+        const uint32_t lo = a[r], hi = rotl(a[r + s], s);
+        a[r] = bfi(mr, lo, hi);
+        a[r + s] = bfi(mr, hi, lo);
       }
   }
+#pragma unroll
+  for (uint32_t r = 1; r < 8; ++r) a[r] = rotl(a[r], 32 - r);
 }
 
 __device__ __forceinline__ uint32_t maj(uint32_t a, uint32_t b, uint32_t c) {
