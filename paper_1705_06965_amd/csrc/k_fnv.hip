@@ -328,9 +328,10 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
     // and the last list is hashed after the link is done.  A launch of few
     // items takes shorter ones still, at least 128 (two per work-group of the
     // default grid) so that every service thread has several, down to 64 KiB.
-    // 1 GiB in 4 KiB items: 20.2 ms with 1 MiB lists, 20.1 with 512 KiB, 19.9
-    // with 256 KiB, 20.0 with 128 KiB; 5,003 items: 585 us with 1 MiB, 495
-    // with 256 KiB, 485 with 128 KiB, 494 with 64 KiB, 554 with 32 KiB.
+    // End to end (with a drain about 40 us longer than today's), 1 GiB in 4 KiB
+    // items: 20.2 ms with 1 MiB lists, 20.1 with 512 KiB, 19.9 with 256 KiB,
+    // 20.0 with 128 KiB; 5,003 items: 585 us with 1 MiB, 495 with 256 KiB, 485
+    // with 128 KiB, 494 with 64 KiB, 554 with 32 KiB.
     A.batch = std::min(wg_size, 256u);
     while (A.batch > 1 && (uint64_t)A.batch * item_bytes > 262144) A.batch = (A.batch + 1) / 2;
     while (A.batch > 1 && n_items < 128ull * A.batch && (uint64_t)A.batch * item_bytes > 65536)
