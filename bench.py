@@ -111,7 +111,8 @@ PROFILES = {
     "tiny": ("profiles/fnv4k_plain_tiny_64.md",
              ["paper_1705_06965_amd/csrc/k_fnv.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp"]),
     "serve": ("profiles/serve_persistent_mix_20k.md",
-              ["paper_1705_06965_amd/csrc/k_serve.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp"]),
+              ["paper_1705_06965_amd/csrc/k_serve.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp",
+               "paper_1705_06965_amd/csrc/host_copy.hpp"]),
     "kv": ("profiles/kv_serve_get_4m.md", ["paper_1705_06965_amd/csrc/k_kv.hip"]),
 }
 
