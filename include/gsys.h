@@ -572,13 +572,15 @@ int gsys_canary(gsys_ctx *ctx, int fd, uint64_t buf, uint64_t n_items, uint64_t 
  *   chunk    bytes per read: a multiple of 64, 64 .. 64 MiB
  *   staging  registered host buffer; each resident work-group uses two
  *            buffers of gsys_wordcount_open_buffer_bytes(chunk) bytes (the
- *            grid shrinks to fit)
+ *            grid of at most 96 work-groups shrinks to fit; environment
+ *            GSYS_PERSISTENT_GRID sets another size)
  *   progress 0, or a registered host buffer of progress_groups x 16 bytes
  *            (the grid shrinks to progress_groups): work-group w keeps
  *            [2w] = (file + 1) << 32 | phase (1 openat, 2 waiting for a
  *            read, 3 scanning, 4 close, 5 no more files) and [2w + 1] =
  *            piece << 32 | low 32 bits of the ticket waited for, stored at
- *            system scope so the host can read them while the kernel runs
+ *            system scope so the host can read them while the kernel runs;
+ *            records that have buffers but no work-group end in phase 5 too
  * Asynchronous on `stream`; gsys_wait drains the host side.  nfiles == 0
  * returns 0 once the shapes (nq, chunk) pass, launching nothing; the
  * pointers may then be null.  Errors: -EINVAL, -EFAULT (paths, staging or

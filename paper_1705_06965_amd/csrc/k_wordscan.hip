@@ -40,11 +40,23 @@ using namespace gsys;
 // Work-groups of 512 (eight 4 KiB sub-blocks of host staging in flight while
 // the previous ones are scanned) scan the 2,000-file corpus as fast as the
 // link delivers it: 4.27 ms with 64 of them and 128 chunk buffers, against
-// 4.49 ms with work-groups of 1,024, whose loads slow the host pool.  Where no
-// work-group has a second chunk or file to go on with, a launch lasts as long
-// as its longest one and 1,024 scan it sooner: 40 files by name 338 -> 285 us.
-// (End to end, with a drain about 40 us longer than today's.)
+// 4.49 ms with work-groups of 1,024, whose loads slow the host pool.  (End to
+// end, with a drain about 40 us longer than today's.)  A launch with few
+// chunks per work-group lasts as long as its longest ones, and 1,024 scan
+// those sooner.  64 work-groups of 1,024 against 512: 90 files in 91 chunks
+// 0.38 against 0.44 ms, 128 0.46 against 0.51, 170 0.50 against 0.52, 800 1.93
+// against 1.85; of 4 KiB each 190 0.35 either way.  By name the same holds for
+// one file per work-group and pieces of at least one round of sub-blocks: 40
+// files with reads of 1 MiB 0.24 against 0.28 ms, of 64 KiB 0.31 against 0.33,
+// of 16 KiB 0.76 against 0.70; 100 files of 4 KiB 0.20 either way but 512
+// ahead by 2%.
 constexpr uint32_t kNarrow = 512, kWide = 1024;
+constexpr uint32_t kFewChunks = 3;  // per work-group
+// Work-groups of the search by name unless GSYS_PERSISTENT_GRID asks for
+// others: more of them, polling host memory, slow the host pool.  2,000 files
+// of 64 KiB with buffers for 256 work-groups: 6.45 ms with 256, 4.88 with 128,
+// 4.71 with 96, 4.99 with 64; 400 files of 4 KiB 0.62, 0.77, 0.60, 0.56.
+constexpr uint32_t kOpenGrid = 96;
 constexpr uint32_t kSeg = 64;                 // bytes scanned per lane per sub-block
 constexpr uint32_t kSB = 64 * kSeg;           // 4 KiB sub-block of a wavefront
 constexpr uint32_t kOverlap = 16;             // max query length and read-ahead
@@ -485,6 +497,7 @@ struct WoArgs {
   uint64_t paths;       // registered host buffer: nfiles x GSYS_PATH_MAX bytes
   int64_t* file_ret;    // device: bytes read per file, or -errno
   uint64_t progress;    // host-visible: 2 x u64 per work-group, or 0
+  uint32_t records;     // of them, the ones that end as kPhDone
   uint32_t nfiles;
   uint32_t chunk;       // bytes per read()
   int32_t dirfd;
@@ -581,6 +594,13 @@ __global__ __launch_bounds__(WG) void wordopen_persistent(WoArgs A) {
     f = grab(A.w, S);
   }
   progress(A, last, kPhDone, 0, 0);
+  // the records of work-groups that were not launched
+  if (A.progress && threadIdx.x == 0)
+    for (uint32_t r = blockIdx.x + gridDim.x; r < A.records; r += gridDim.x) {
+      uint64_t* p = reinterpret_cast<uint64_t*>(A.progress) + 2ull * r;
+      st_sys(p + 1, 0);
+      st_sys(p, kPhDone);
+    }
 }
 
 // Clear the counts and the work counter before a scan.
@@ -641,7 +661,8 @@ int gsys_wordscan(gsys_ctx* ctx, uint64_t chunks, uint32_t n_chunks, uint32_t ch
     if (n_chunks && staging_bytes < per_wg) return -EINVAL;
     const uint64_t items = (uint64_t)n_chunks * passes;
     // as many work-groups as are resident, have staging and have a chunk
-    const bool wide = items <= staging_bytes / per_wg;
+    const uint64_t groups = std::min<uint64_t>(staging_bytes / per_wg, gsys_internal::cu_count(ctx));
+    const bool wide = items <= kFewChunks * groups;
     const void* kp = wide ? (const void*)wordscan_persistent<kWide>
                           : (const void*)wordscan_persistent<kNarrow>;
     const uint32_t block = wide ? kWide : kNarrow;
@@ -714,16 +735,18 @@ int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfile
   hipLaunchKernelGGL(zero_counts, dim3((uint32_t)std::min<uint64_t>((ncount + 255) / 256, 4096)),
                      dim3(256), 0, s, (uint32_t*)counts, ncount, (uint32_t*)A.w.work);
   if (hipGetLastError() != hipSuccess) return -ENODEV;
-  const bool wide = nfiles <= staging_bytes / per_wg;
+  const uint32_t req = gsys_internal::persistent_grid_override(ctx);
+  uint64_t groups = std::min<uint64_t>({staging_bytes / per_wg, nfiles, gsys_internal::cu_count(ctx)});
+  if (progress && progress_groups < groups) groups = progress_groups;  // one record per work-group
+  A.records = (uint32_t)groups;
+  groups = std::min<uint64_t>(groups, req ? req : kOpenGrid);
+  const bool wide = nfiles <= groups && chunk >= (kWide / 64) * kSB;
   const void* kp = wide ? (const void*)wordopen_persistent<kWide>
                         : (const void*)wordopen_persistent<kNarrow>;
   const uint32_t block = wide ? kWide : kNarrow;
   uint32_t grid = gsys_internal::resident_grid(ctx, kp, block, 0);
   if (!grid) return -ENODEV;
-  grid = (uint32_t)std::min<uint64_t>({(uint64_t)grid, staging_bytes / per_wg, (uint64_t)nfiles});
-  const uint32_t req = gsys_internal::persistent_grid_override(ctx);
-  if (req && req < grid) grid = req;
-  if (progress && progress_groups < grid) grid = progress_groups;  // one record per work-group
+  grid = (uint32_t)std::min<uint64_t>(grid, groups);
   A.progress = progress;
   void* args[] = {&A};
   return gsys_internal::launch(ctx, kp, grid, block, 0, args, s);

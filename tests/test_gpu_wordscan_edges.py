@@ -94,3 +94,35 @@ def test_open_edges_match_oracle(gs, tmpdata, chunk):
     r.close()
     assert ret.tolist() == [os.path.getsize(p) for p in paths]
     assert (counts == want).all(), np.argwhere(counts != want)[:10]
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 6, 7, 97, 193])
+def test_width_and_grid_rules(gs, tmpdata, n):
+    """File counts on both sides of the lines between wide and narrow
+    work-groups (two of them, and the 96 of the search by name) and past the
+    grid; every progress record ends."""
+    g, ctx = gs
+    from paper_1705_06965_amd.wordscan import WordOpenRunner, WordScanRunner
+    rng = np.random.default_rng(n)
+    d = os.path.join(tmpdata, "rules%d" % n)
+    os.makedirs(d, exist_ok=True)
+    names = []
+    for i in range(n):
+        words = [QUERIES[k] for k in rng.integers(0, len(QUERIES), rng.integers(0, 3000))]
+        names.append("f%d.txt" % i)
+        with open(os.path.join(d, names[-1]), "wb") as f:
+            f.write(b" ".join(words))
+    paths = [os.path.join(d, x) for x in names]
+    want = oracle.wordcount(paths, QUERIES)
+    print("rules", n, flush=True)
+    r = WordScanRunner(ctx, paths, QUERIES, persistent_buffers=4)
+    assert (r.run(g.PERSISTENT) == want).all()
+    assert (r.run(g.GRAPH) == want).all()
+    r.close()
+    for groups, chunk in ((2, 4096), (2, 65536), (2, 1 << 18), (256, 1 << 18)):
+        r = WordOpenRunner(ctx, d, names, QUERIES, chunk=chunk, groups=groups)
+        print("rules by name", n, groups, chunk, flush=True)
+        got, ret = r.run()
+        assert (got == want).all() and ret.tolist() == [os.path.getsize(p) for p in paths]
+        assert all(p[1] == 5 for p in r.progress_records())
+        r.close()
