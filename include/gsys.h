@@ -153,7 +153,8 @@ int gsys_register_buffer(gsys_ctx *ctx, uint64_t dev_addr, void *host_addr, uint
 /*
  * Drop a registration.  Tickets the GPU has claimed may still name the
  * buffer, so while the host has not serviced every claimed ticket (after
- * waiting up to 10 ms for them) the call fails with -EBUSY and keeps it.
+ * waiting up to 10 ms for them, and up to 2 s for the device to say how many
+ * it has claimed) the call fails with -EBUSY and keeps it.
  * On success it returns only once no service thread can still be using the
  * buffer's memory: the caller may free it then.  Errors: -ENOENT, -EBUSY.
  */
@@ -214,9 +215,10 @@ int gsys_launch(gsys_ctx *ctx, const gsys_launch_desc *desc, void *stream);
 /*
  * Drain (section 8.3: a CPU-side call that makes sure every GPU system call
  * has completed).  Reads how many tickets the GPU has claimed and waits until
- * the host has serviced all of them, or `timeout_ns` passed (0 = forever).
+ * the host has serviced all of them, or `timeout_ns` passed (0 = forever;
+ * the device is given at least 0.1 s to hand the number over).
  * Call it after the issuing kernels finished to drain everything.
- * Errors: -ETIMEDOUT.
+ * Errors: -ETIMEDOUT, -ENODEV (the number could not be read).
  */
 int gsys_wait(gsys_ctx *ctx, uint64_t timeout_ns);
 
@@ -242,7 +244,10 @@ typedef struct gsys_stats {
  * Snapshot the counters since the last reset; reset != 0 makes this
  * snapshot the new zero.  Each poller counts in its own block and the
  * snapshot sums them, so counts from calls still being completed may land
- * in the next snapshot.  retired_lo and claimed are read, never reset.
+ * in the next snapshot.  retired_lo and claimed are read, never reset.  If
+ * the device does not hand the claimed count over within 2 s, or it cannot be
+ * read (-ENODEV, the other counters hold), claimed counts the requests that
+ * the host has seen in the ring.
  */
 int gsys_stats_get(gsys_ctx *ctx, gsys_stats *out, int reset);
 
@@ -261,8 +266,9 @@ int64_t gsys_ledger(gsys_ctx *ctx, uint64_t *out, uint64_t max, int reset);
  * Stop the pool: drain with `timeout_ns`, complete every request still in the
  * ring with -ESHUTDOWN so GPU waiters return, join the threads, free the ring,
  * the completion records and every gsys_host_alloc() buffer.  ctx is invalid
- * afterwards.  Returns 0, or -ETIMEDOUT if the drain timed out (the context is
- * torn down all the same).
+ * afterwards.  Returns 0, -ETIMEDOUT if the drain timed out or -ENODEV if it
+ * could not read how many tickets are claimed (the context is torn down all the
+ * same, and waiting requests are answered).
  */
 int gsys_shutdown(gsys_ctx *ctx, uint64_t timeout_ns);
 

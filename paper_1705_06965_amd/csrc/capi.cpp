@@ -11,8 +11,6 @@
 #include <time.h>
 #include <unistd.h>
 
-#include <immintrin.h>
-
 #include <hip/hip_runtime.h>
 #include <hsa/amd_hsa_signal.h>
 #include <hsa/hsa.h>
@@ -25,6 +23,7 @@
 #include <thread>
 #include <vector>
 
+#include "counter_read.hpp"
 #include "gsys.h"
 #include "host_pool.hpp"
 #include "kernels.hpp"
@@ -102,8 +101,9 @@ struct gsys_ctx {
   gsys_slot* ring = nullptr;       // host view
   gsys_comp* comp = nullptr;       // host view
   // host-coherent page: [0] retired_lo, [32] the ticket counter of NO_DEVICE
-  // contexts, [40] the device's ticket counter as last read, [64] sleeping pollers, [96..97] serving control words; each
-  // group on its own 256-byte line
+  // contexts, [40] the device's ticket counter as last read, [64] sleeping
+  // pollers, [96..97] serving control words; each group on its own 256-byte
+  // line
   uint64_t* host_words = nullptr;
   gsys_slot* ring_dev = nullptr;
   gsys_comp* comp_dev = nullptr;
@@ -114,7 +114,7 @@ struct gsys_ctx {
   gsys_host::Pool* pool = nullptr;
   hipStream_t aux = nullptr;
   std::mutex mu;
-  std::mutex drain_mu;             // host_words[40] while claimed_tickets() fills it
+  gsys_host::CounterRead counter;  // host_words[40]
   std::map<void*, std::pair<uint64_t, uint32_t>> host_allocs;  // host ptr -> (bytes, id)
   uint8_t* arena = nullptr;
   uint64_t arena_bytes = 0;
@@ -185,28 +185,53 @@ void host_coherent_free(gsys_ctx* c, void* host) {
   else hipHostFree(host);
 }
 
-uint64_t claimed_tickets(gsys_ctx* c) {
-  if (c->no_device) return __atomic_load_n(&c->host_words[32], __ATOMIC_ACQUIRE);
-  // A one-thread kernel stores the counter into the context's pinned page and
-  // the host watches that word: 9 us, against 21 for a copy to pageable memory
-  // and a stream synchronisation, 13 for one to pinned memory.
-  constexpr uint64_t kUnset = ~0ull;  // no ticket gets that far
-  std::lock_guard<std::mutex> g(c->drain_mu);
-  hipSetDevice(c->device);
-  __atomic_store_n(&c->host_words[40], kUnset, __ATOMIC_RELEASE);
-  if (!gsys_internal::launch_read_tail ||
-      !gsys_internal::launch_read_tail(c->dev_words, (uint64_t)(c->retired_lo_dev + 40), c->aux))
+// How long a call that names no time-out of its own, or a shorter one, waits
+// for the device to hand over its ticket counter.
+constexpr uint64_t kReadNs = 2000000000ull;      // removal, statistics, shutdown
+constexpr uint64_t kWaitReadNs = 100000000ull;   // gsys_wait
+
+// The tickets the GPU has claimed (deadline: now_ns() time, 0 = none).
+int claimed_tickets(gsys_ctx* c, uint64_t deadline, uint64_t* out) {
+  if (c->no_device) {
+    *out = __atomic_load_n(&c->host_words[32], __ATOMIC_ACQUIRE);
     return 0;
-  uint64_t v;
-  for (uint32_t spins = 1; (v = __atomic_load_n(&c->host_words[40], __ATOMIC_ACQUIRE)) == kUnset; ++spins) {
-    _mm_pause();
-    // a kernel that ended without storing (a failed device) ends the wait too
-    if ((spins & 0xffff) == 0 && hipStreamQuery(c->aux) != hipErrorNotReady) {
-      v = __atomic_load_n(&c->host_words[40], __ATOMIC_ACQUIRE);
-      return v == kUnset ? 0 : v;
+  }
+  hipSetDevice(c->device);
+  return c->counter.read(
+      &c->host_words[40], deadline,
+      [&] {
+        return gsys_internal::launch_read_tail &&
+               gsys_internal::launch_read_tail(c->dev_words, (uint64_t)(c->retired_lo_dev + 40),
+                                               c->aux);
+      },
+      [&] {
+        const hipError_t e = hipStreamQuery(c->aux);
+        return e == hipErrorNotReady ? gsys_host::CounterRead::kBusy
+               : e == hipSuccess     ? gsys_host::CounterRead::kIdle
+                                     : gsys_host::CounterRead::kFailed;
+      },
+      out);
+}
+
+// Wait until the host has serviced every ticket claimed by now, or timeout_ns
+// passed (0 = forever); the device has at least read_ns to say how many.
+int drain(gsys_ctx* c, uint64_t timeout_ns, uint64_t read_ns) {
+  const uint64_t t0 = now_ns();
+  uint64_t want = 0;
+  if (int e = claimed_tickets(c, timeout_ns ? t0 + std::max(timeout_ns, read_ns) : 0, &want))
+    return e;
+  uint32_t spins = 0;
+  while (c->pool->serviced() < want) {
+    if (timeout_ns && now_ns() - t0 > timeout_ns) return -ETIMEDOUT;
+    if (++spins < 1000) {
+      std::this_thread::yield();
+    } else {
+      timespec ts{0, 20000};
+      nanosleep(&ts, nullptr);
     }
   }
-  return v;
+  c->pool->retire_scan();
+  return 0;
 }
 
 // The HIP device's HSA agent (matched by PCI location).
@@ -450,7 +475,7 @@ int gsys_register_buffer(gsys_ctx* c, uint64_t dev, void* host, uint64_t bytes, 
 // Outstanding tickets may still reference any buffer: claimed tickets that
 // the pool has not all serviced after a short wait make a removal -EBUSY.
 static int quiet_for_removal(gsys_ctx* c) {
-  return gsys_wait(c, 10000000) ? -EBUSY : 0;
+  return drain(c, 10000000, kReadNs) ? -EBUSY : 0;
 }
 
 int gsys_unregister_buffer(gsys_ctx* c, uint32_t id) {
@@ -521,27 +546,15 @@ int gsys_device_ctx(gsys_ctx* c, gsys_dev_ctx* out) {
 
 int gsys_wait(gsys_ctx* c, uint64_t timeout_ns) {
   if (!c) return -EINVAL;
-  const uint64_t want = claimed_tickets(c);
-  const uint64_t t0 = now_ns();
-  uint32_t spins = 0;
-  while (c->pool->serviced() < want) {
-    if (timeout_ns && now_ns() - t0 > timeout_ns) return -ETIMEDOUT;
-    if (++spins < 1000) {
-      std::this_thread::yield();
-    } else {
-      timespec ts{0, 20000};
-      nanosleep(&ts, nullptr);
-    }
-  }
-  c->pool->retire_scan();
-  return 0;
+  return drain(c, timeout_ns, kWaitReadNs);
 }
 
 int gsys_stats_get(gsys_ctx* c, gsys_stats* out, int reset) {
   if (!c || !out) return -EINVAL;
   c->pool->stats(out, reset);
-  out->claimed = claimed_tickets(c);
-  return 0;
+  const int e = claimed_tickets(c, now_ns() + kReadNs, &out->claimed);
+  if (e) out->claimed = c->pool->published();
+  return e == -ETIMEDOUT ? 0 : e;
 }
 
 int64_t gsys_ledger(gsys_ctx* c, uint64_t* out, uint64_t max, int reset) {
@@ -551,9 +564,9 @@ int64_t gsys_ledger(gsys_ctx* c, uint64_t* out, uint64_t max, int reset) {
 
 int gsys_shutdown(gsys_ctx* c, uint64_t timeout_ns) {
   if (!c) return -EINVAL;
-  int rc = gsys_wait(c, timeout_ns ? timeout_ns : 1);
+  int rc = drain(c, timeout_ns ? timeout_ns : 1, kReadNs);
   c->pool->stop_and_join();
-  c->pool->poison_outstanding(claimed_tickets(c));
+  c->pool->poison_outstanding();
   if (!c->no_device) {
     hipSetDevice(c->device);
     hipDeviceSynchronize();

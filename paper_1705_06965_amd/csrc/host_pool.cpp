@@ -945,23 +945,35 @@ void Pool::poller(int idx) {
   tls_ctr_ = nullptr;
 }
 
-uint64_t Pool::poison_outstanding(uint64_t claimed) {
+uint64_t Pool::poison_outstanding() {
   // runs after the pollers stopped: every request still READY (or taken
   // but never completed) is answered with -ESHUTDOWN so that GPU waiters
-  // return instead of waiting for the watchdog
-  uint64_t lo = __atomic_load_n(retired_lo_, __ATOMIC_RELAXED);
+  // return instead of waiting for the watchdog.  The slots say which they
+  // are: the device need not answer for it
+  const uint64_t lo = __atomic_load_n(retired_lo_, __ATOMIC_RELAXED);
   uint64_t n = 0;
-  for (uint64_t t = lo; t < claimed; ++t) {
-    gsys_slot* sl = &ring_[t & (D_ - 1)];
-    uint64_t c = ld_acq(&sl->ctl);
-    if (c == GSYS_CTL(t, GSYS_ST_READY) || c == GSYS_CTL(t, GSYS_ST_PROCESSING) ||
-        c == GSYS_CTL(t, kQueued)) {
+  for (uint64_t k = 0; k < D_; ++k) {
+    gsys_slot* sl = &ring_[(lo + k) & (D_ - 1)];
+    const uint64_t c = ld_acq(&sl->ctl), t = GSYS_CTL_TICKET(c);
+    const uint32_t st = GSYS_CTL_STATE(c);
+    if (sl == &ring_[t & (D_ - 1)] &&
+        (st == GSYS_ST_READY || st == GSYS_ST_PROCESSING || st == kQueued)) {
       complete(t, sl, -ESHUTDOWN);
       bump(ctr().ehist[5], 1);
       ++n;
     }
   }
   ctr().serviced.fetch_add(n, std::memory_order_release);
+  return n;
+}
+
+uint64_t Pool::published() const {
+  uint64_t n = 0;
+  for (uint64_t i = 0; i < D_; ++i) {
+    const uint64_t c = ld_acq(&ring_[i].ctl), t = GSYS_CTL_TICKET(c);
+    if (GSYS_CTL_STATE(c) != GSYS_ST_FREE) n = std::max(n, t + 1);
+    else if (t >= D_) n = std::max(n, t - D_ + 1);  // free again after ticket t - D
+  }
   return n;
 }
 

@@ -139,8 +139,11 @@ class Pool {
     return n;
   }
   // Complete every request still READY with -ESHUTDOWN (called after the
-  // pollers stopped).  `claimed` bounds the tickets examined.
-  uint64_t poison_outstanding(uint64_t claimed);
+  // pollers stopped).
+  uint64_t poison_outstanding();
+  // Tickets up to the highest one whose slot its caller has filled: at most as
+  // many as are claimed.
+  uint64_t published() const;
   void retire_scan();
 
   // true if [dev, dev + len) lies inside one registered host buffer
