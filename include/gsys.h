@@ -348,8 +348,8 @@ typedef struct gsys_chunk {
  *             (every file empty, or nfiles == 0) launches only the zeroing
  *             of counts; chunks may then be 0
  *   queries   device uint8[nq * 16], query q in bytes [16q, 16q + qlens[q]);
- *             1 <= qlens[q] <= 16, no delimiter bytes, all distinct;
- *             1 <= nq <= 64
+ *             1 <= qlens[q] <= 16, no delimiter bytes, all distinct (of
+ *             equal ones the first gets the counts); 1 <= nq <= 64
  *   counts    device uint32[nfiles * nq], zeroed by the call
  *   staging   registered GSYS_BUF_HOST buffer of staging_bytes; the plain
  *             form needs n_chunks * cbuf bytes, the persistent forms 2 * cbuf

@@ -150,19 +150,34 @@ __device__ void build_table(const WsArgs& A, Shared<WG>& S) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) S.mask[q][i] = byte_mask((int32_t)q - 4 * i);
   __builtin_amdgcn_wave_barrier();
+  uint32_t len = 0, k = 0;
+  u32x4 w = {0, 0, 0, 0};
   if (q < A.nq) {
-    const uint32_t len = A.qlens[q];
+    len = A.qlens[q];
     const uint32_t* qp = reinterpret_cast<const uint32_t*>(A.queries + q * 16);
-    u32x4 w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = qp[i] & byte_mask((int32_t)len - 4 * i);
-    const uint32_t k = token_key(w, len);
+    k = token_key(w, len);
     uint32_t s = k & (kTab - 1);
     while (atomicCAS(&S.tkey[s], 0u, k) != 0u) s = (s + 1) & (kTab - 1);
     S.tq[s] = (int32_t)(q | (len << 16));
     S.qw[s] = w;
     const uint32_t f = filter_bit(w.x, len);
     atomicOr(&S.filter[f >> 5], 1u << (f & 31u));
+  }
+  __builtin_amdgcn_wave_barrier();
+  // Of equal queries the first gets the counts, whichever lane's entry a
+  // lookup meets first: all of them find that entry here and the lowest index
+  // goes into it.
+  if (q < A.nq) {
+    uint32_t s = k & (kTab - 1);
+    for (;; s = (s + 1) & (kTab - 1)) {
+      const u32x4 o = S.qw[s];
+      if (S.tkey[s] == k && o.x == w.x && o.y == w.y && o.z == w.z && o.w == w.w &&
+          (uint32_t)S.tq[s] >> 16 == (len & 0xffffu))
+        break;
+    }
+    atomicMin(&S.tq[s], (int32_t)(q | (len << 16)));
   }
 }
 
