@@ -595,6 +595,9 @@ int gsys_canary(gsys_ctx *ctx, int fd, uint64_t buf, uint64_t n_items, uint64_t 
 /* Bytes of one piece buffer of gsys_wordcount_open for reads of `chunk`
  * bytes: the carried bytes, the piece and the scanner's window past it. */
 uint64_t gsys_wordcount_open_buffer_bytes(uint32_t chunk);
+/* Work-groups that gsys_wordcount_open launches at most in this context:
+ * staging and progress records for more are not used. */
+uint32_t gsys_wordcount_open_groups(gsys_ctx *ctx);
 int gsys_wordcount_open(gsys_ctx *ctx, int dirfd, uint64_t paths, uint32_t nfiles,
                         uint64_t queries, uint64_t qlens, uint32_t nq, uint64_t counts,
                         uint64_t file_ret, uint32_t chunk, uint64_t staging,

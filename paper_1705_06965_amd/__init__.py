@@ -136,6 +136,7 @@ _SIGS = {
                                     C.c_uint32, C.c_uint64, C.c_uint64, _P, C.c_uint32, _P, _P,
                                     _P]),
     "gsys_wordcount_open_buffer_bytes": (C.c_uint64, [C.c_uint32]),
+    "gsys_wordcount_open_groups": (C.c_uint32, [_P]),
     "gsys_host_pread_rate": (C.c_int, [_P, _P, _P, C.c_uint64, C.c_uint64, C.c_uint64,
                                        C.c_uint64, C.c_uint32, C.c_uint32,
                                        C.POINTER(C.c_double)]),

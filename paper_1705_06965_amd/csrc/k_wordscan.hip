@@ -708,6 +708,12 @@ uint64_t gsys_wordcount_open_buffer_bytes(uint32_t chunk) {
   return ((uint64_t)kOpenHead + chunk + kOpenTail + 15) & ~15ull;
 }
 
+uint32_t gsys_wordcount_open_groups(gsys_ctx* ctx) {
+  if (!ctx) return 0;
+  const uint32_t req = gsys_internal::persistent_grid_override(ctx);
+  return req ? req : kOpenGrid;
+}
+
 int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfiles,
                         uint64_t queries, uint64_t qlens, uint32_t nq, uint64_t counts,
                         uint64_t file_ret, uint32_t chunk, uint64_t staging,
@@ -750,11 +756,10 @@ int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfile
   hipLaunchKernelGGL(zero_counts, dim3((uint32_t)std::min<uint64_t>((ncount + 255) / 256, 4096)),
                      dim3(256), 0, s, (uint32_t*)counts, ncount, (uint32_t*)A.w.work);
   if (hipGetLastError() != hipSuccess) return -ENODEV;
-  const uint32_t req = gsys_internal::persistent_grid_override(ctx);
   uint64_t groups = std::min<uint64_t>({staging_bytes / per_wg, nfiles, gsys_internal::cu_count(ctx)});
   if (progress && progress_groups < groups) groups = progress_groups;  // one record per work-group
   A.records = (uint32_t)groups;
-  groups = std::min<uint64_t>(groups, req ? req : kOpenGrid);
+  groups = std::min<uint64_t>(groups, gsys_wordcount_open_groups(ctx));
   const bool wide = nfiles <= groups && chunk >= (kWide / 64) * kSB;
   const void* kp = wide ? (const void*)wordopen_persistent<kWide>
                         : (const void*)wordopen_persistent<kNarrow>;

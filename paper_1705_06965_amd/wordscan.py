@@ -162,7 +162,8 @@ class WordOpenRunner:
         self.counts = torch.zeros(max(1, self.nfiles * self.nq), dtype=torch.int32, device=device)
         self.file_ret = torch.zeros(max(1, self.nfiles), dtype=torch.int64, device=device)
         self.back = Readback(self.counts, self.file_ret)
-        self.groups = max(1, min(groups, self.nfiles))
+        # buffers and records for as many work-groups as a launch has at most
+        self.groups = max(1, min(groups, self.nfiles, lib.gsys_wordcount_open_groups(ctx.h)))
         self.staging_bytes = 2 * open_buffer_bytes(chunk) * self.groups
         self.staging = ctx.host_alloc(self.staging_bytes)
         # per work-group progress records (host memory the kernel writes at

@@ -46,3 +46,23 @@ def test_empty_chunk_table_is_a_valid_call():
         st.free()
     finally:
         c.shutdown()
+
+
+def test_search_by_name_allocates_for_the_work_groups_it_launches(tmp_path, monkeypatch):
+    """Piece buffers and progress records for as many work-groups as a launch
+    has at most, which the environment can raise; fewer files need fewer."""
+    import paper_1705_06965_amd as g
+    from paper_1705_06965_amd.wordscan import WordOpenRunner, open_buffer_bytes
+    for grid, want in ((None, 96), ("200", 200), ("1000", 256)):
+        if grid:
+            monkeypatch.setenv("GSYS_PERSISTENT_GRID", grid)
+        c = g.Context(flags=g.CFG_NO_DEVICE | g.CFG_NO_PIN, service_threads=1)
+        try:
+            for names, groups in ((300, want), (7, 7)):
+                r = WordOpenRunner(c, str(tmp_path), ["f%d" % i for i in range(names)], [b"x"],
+                                   chunk=4096, device="cpu")
+                assert r.groups == len(r.progress_records()) == groups
+                assert r.staging.nbytes == 2 * open_buffer_bytes(4096) * groups
+                r.close()
+        finally:
+            c.shutdown()
