@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fnv_rules.hpp"
 #include "gsys_device.hpp"
 
 namespace gsys_k {
@@ -153,16 +154,10 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
 
 constexpr uint64_t kFnvPrime = 0x100000001b3ull;
 constexpr uint64_t kFnvBasis = 0xcbf29ce484222325ull;
-constexpr uint32_t kSegBytes = 128;               // per lane and step
-constexpr uint32_t kStepBytes = 64 * kSegBytes;   // per wavefront and step
 constexpr uint32_t kColBytes = 4 * kSegBytes;     // summed by one MFMA column
 constexpr uint32_t kSegStride = kSegBytes + 16;   // in LDS: conflict-free 16-byte reads
 // Wave tile: the step's bytes, then the byte counts of two groups of items.
 constexpr uint32_t kParTile = 64 * kSegStride + 2 * 16 * 4;
-// Items up to this size are hashed one per lane (wave_fnv_t): a matrix column
-// sums 512 bytes of one item, so a shorter one would waste lanes, and its
-// chain is short (8 us for 512 bytes).
-constexpr uint32_t kParMinItem = 512;
 
 struct FnvWeights {
   // [t * 2 + half][lane][register]: four digits of one plane per register
@@ -262,19 +257,6 @@ __device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
   const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
   const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
   return ((uint64_t)hi << 32) | lo;
-}
-
-// Lanes an item occupies in a step (a power of two of at least one column, at
-// most the wavefront) as a shift.
-__host__ __device__ inline uint32_t par_lanes_log2(uint32_t item_bytes) {
-  uint32_t k = 2;
-  while (k < 6 && (kSegBytes << k) < item_bytes) ++k;
-  return k;
-}
-
-// The items a wavefront takes at once.
-__host__ __device__ inline uint32_t par_items(uint32_t item_bytes) {
-  return 64u >> par_lanes_log2(item_bytes);
 }
 
 // The sum of the item's (x - s) p^(bytes to the end of its slot of 128 << ll

@@ -42,11 +42,6 @@ struct FnvArgs {
   uint32_t batch;  // persistent forms: items per list call (wg is the same)
 };
 
-// Threads of the widest block of a kernel variant: of the variants that hash
-// items with many lanes, up to 512 work-items hold the next step's bytes and
-// the weights in registers (256 per lane), wider ones do not (128 per lane).
-constexpr uint32_t kParBlock = 512;
-
 // Staging address of item `item` of batch `bt` (slot = item - bt * batch).
 __device__ __forceinline__ uint64_t stage_addr(const FnvArgs& A, uint64_t bt, uint32_t batch,
                                                uint64_t item) {
@@ -90,7 +85,7 @@ __device__ __forceinline__ void consume_items(const FnvArgs& A, uint64_t first, 
       hi = min(cnt, lo + 64);
       step = items;
     }
-    wave_fnv_par<(WGMAX <= kParBlock)>(
+    wave_fnv_par<true>(
         row0, A.item_bytes, lo, step, hi, lds + wave * kParTile,
         [&](uint64_t i) { return lens[i]; },
         [&](uint64_t i, uint64_t h) { A.out_fnv[first + i] = h; });
@@ -310,12 +305,8 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   A.wg = wg_size;
   A.batch = wg_size;
   hipStream_t s = (hipStream_t)stream;
-  // Many lanes per item, except in work-groups of 1,024 (128 registers per
-  // lane: they spill and load nothing ahead; 8,000 work-item preads of 4 KiB
-  // took 2.1 ms against 1.0 ms) unless the chain is long.
-  bool par = item_bytes > (wg_size <= kParBlock ? kParMinItem : 16384u);
-  // the kernel variant's widest block: see kParBlock and chunk_for
-  bool small = wg_size <= (par ? kParBlock : 256u);
+  bool par = false;  // many lanes per item
+  bool small = wg_size <= 256;  // the chain variant's block: see chunk_for
   uint32_t block = wg_size;
   auto lds_for = [&](uint32_t threads) {
     return par ? (threads / 64) * kParTile + A.wg * 4
@@ -373,28 +364,29 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   const uint32_t gran = GSYS_CELL_GRAN(cell);
   const bool strong = (cell & GSYS_CELL_STRONG) != 0;
   const bool blocking = (cell & GSYS_CELL_BLOCKING) != 0;
-  // Work-item calls do not depend on the work-group.  A launch that leaves
-  // compute units idle is spread over more and smaller work-groups, down to
-  // one step of hashing for each of their eight wavefronts.  With a call's
-  // launch, reads and drain, against one work-group per wg_size items: 64
-  // items of 4 KiB 57.5 against 68.0 us, 300 of 64 KiB 452 against 567, 20 of
-  // 1 MiB 0.75 against 1.36 ms.
+  // Helper wavefronts share the items of the work-group after a barrier, so
+  // of a work-group with several calling wavefronts none hashes before the
+  // last call of all is done: more than 64 work-item calls per work-group (a
+  // launch that fills the compute units) go without.  60,000 of 4 KiB in
+  // work-groups of 256: 6.2 ms without, 6.9 with.
   const uint32_t cus = gsys_internal::cu_count(ctx);
   if (gran == GSYS_GRAN_WI && item_bytes > kParMinItem) {
-    while (A.wg > 8 * par_items(item_bytes) && (n_items + A.wg / 2 - 1) / (A.wg / 2) <= cus)
-      A.wg /= 2;
-    if (A.wg <= kParBlock) par = small = true;
-    block = std::max(64u, A.wg);
+    A.wg = spread_group(n_items, item_bytes, wg_size, cus);
+    par = A.wg <= 64 || many_lanes(n_items, item_bytes, A.wg, A.wg);
+    block = A.wg > 64 ? A.wg : helped_block(64, ceil_div(n_items, A.wg), cus);
+  } else if (gran != GSYS_GRAN_WI && item_bytes > kParMinItem) {
+    const uint32_t helped = helped_block(wg_size, ceil_div(n_items, wg_size), cus);
+    par = many_lanes(n_items, item_bytes, wg_size, helped);
+    if (par) block = helped;
   }
   const uint64_t grid64 = (n_items + A.wg - 1) / A.wg;
   if (grid64 > 0x7fffffffull) return -EINVAL;
   const uint32_t grid = (uint32_t)grid64;
   const void* k = nullptr;
 #define GSYS_PLAIN_K(G_, O_, B_)                                                   \
-  (par ? (small ? (const void*)fnv4k_plain<G_, O_, B_, kParBlock, true>            \
-                : (const void*)fnv4k_plain<G_, O_, B_, 1024, true>)                \
-       : (small ? (const void*)fnv4k_plain<G_, O_, B_, 256, false>                 \
-                : (const void*)fnv4k_plain<G_, O_, B_, 1024, false>))
+  (par     ? (const void*)fnv4k_plain<G_, O_, B_, kParBlock, true>                 \
+   : small ? (const void*)fnv4k_plain<G_, O_, B_, 256, false>                      \
+           : (const void*)fnv4k_plain<G_, O_, B_, 1024, false>)
   if (gran == GSYS_GRAN_WI) {
     if (!strong) return -EINVAL;  // work-item calls are implicitly strong
     k = blocking ? GSYS_PLAIN_K(G::WorkItem, O::Strong, B::Blocking)
@@ -420,13 +412,6 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
     return -EINVAL;
   }
 #undef GSYS_PLAIN_K
-  // Few work-groups leave compute units idle while theirs hash: helper
-  // wavefronts (they make no calls), up to eight per compute unit, share the
-  // group's items.  A kernel of one work-group of 64 work-items, one list call
-  // and 64 items of 4 KiB takes 94 us with its one wavefront, 42 with eight.
-  if (par)
-    while (block * 2 <= kParBlock && (uint64_t)grid * block * 2 <= (uint64_t)cus * kParBlock)
-      block *= 2;
   void* args[] = {&A};
   return gsys_internal::launch(ctx, k, grid, block, lds_for(block), args, s);
 }
