@@ -85,9 +85,14 @@ inline bool many_lanes(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t bl
 // is spread over more and smaller work-groups, down to one step of hashing for
 // each of their eight wavefronts.  With a call's launch, reads and drain,
 // against one work-group per wg items: 64 items of 4 KiB 57.5 against 68.0 us,
-// 300 of 64 KiB 452 against 567, 20 of 1 MiB 0.75 against 1.36 ms.
-constexpr uint32_t spread_group(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t cus) {
-  if (item_bytes <= kParMinItem) return wg;
+// 300 of 64 KiB 452 against 567, 20 of 1 MiB 0.75 against 1.36 ms.  Not with
+// more calls than the ring has slots: those that wait for one poll host
+// memory, and from more compute units they slow the host more: 100,000 calls
+// of 576 bytes in work-groups of 1,024 (98 of them, a ring of 65,536) 11.0 ms,
+// spread 13.1.
+constexpr uint32_t spread_group(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t cus,
+                                uint64_t slots) {
+  if (item_bytes <= kParMinItem || n > slots) return wg;
   while (wg > 8 * par_items(item_bytes) && ceil_div(n, wg / 2) <= cus) wg /= 2;
   return wg;
 }

@@ -371,7 +371,7 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   // work-groups of 256: 6.2 ms without, 6.9 with.
   const uint32_t cus = gsys_internal::cu_count(ctx);
   if (gran == GSYS_GRAN_WI && item_bytes > kParMinItem) {
-    A.wg = spread_group(n_items, item_bytes, wg_size, cus);
+    A.wg = spread_group(n_items, item_bytes, wg_size, cus, A.c.ring_mask + 1);
     par = A.wg <= 64 || many_lanes(n_items, item_bytes, A.wg, A.wg);
     block = A.wg > 64 ? A.wg : helped_block(64, ceil_div(n_items, A.wg), cus);
   } else if (gran != GSYS_GRAN_WI && item_bytes > kParMinItem) {

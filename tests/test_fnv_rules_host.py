@@ -16,6 +16,9 @@ WRAPPER = """
 extern "C" int group_rule(uint64_t n, uint32_t item, uint32_t wg, uint32_t cus) {
   return gsys_k::many_lanes(n, item, wg, gsys_k::helped_block(wg, gsys_k::ceil_div(n, wg), cus));
 }
+extern "C" int spread_rule(uint64_t n, uint32_t item, uint32_t wg, uint32_t cus, uint64_t slots) {
+  return gsys_k::spread_group(n, item, wg, cus, slots);
+}
 extern "C" int item_rule(uint64_t n, uint32_t item, uint32_t wg) {
   return gsys_k::many_lanes(n, item, wg, wg);
 }
@@ -35,6 +38,7 @@ def rules(tmp_path_factory):
     assert b.returncode == 0, b.stderr
     lib = C.CDLL(so)
     lib.group_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32]
+    lib.spread_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint64]
     lib.item_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32]
     return lib
 
@@ -66,3 +70,11 @@ def test_work_item_calls_that_fill_the_chip(rules, n, wg, many):
     chains unless those would read the link in 128-byte pieces."""
     assert rules.item_rule(n, 4096, wg) == many
 
+
+@pytest.mark.parametrize("n,item,wg,slots,want", [
+    (64, 4096, 64, 65536, 16), (8000, 4096, 1024, 65536, 32), (60000, 576, 1024, 65536, 256),
+    (65536, 576, 1024, 65536, 256), (65537, 576, 1024, 65536, 1024),
+    (100000, 576, 1024, 65536, 1024), (100000, 576, 1024, 1 << 18, 512), (5000, 4096, 1024, 4096, 1024),
+    (20, 1 << 20, 64, 64, 8), (300, 256, 64, 65536, 64)])
+def test_spread_keeps_to_launches_that_fit_the_ring(rules, n, item, wg, slots, want):
+    assert rules.spread_rule(n, item, wg, CUS, slots) == want
