@@ -11,6 +11,13 @@ from . import (Context, FD_READ, PLAIN, PERSISTENT, GRAPH, Readback, check, lib,
                _stream)
 
 
+# Runs of this many items clear the results first.  The kernel that does it
+# costs 3 us, and a launch of more calls than the ring has slots is faster after
+# one, whatever it does: the work-item calls of 200,000 items of 1 KiB take 21.0
+# ms, 23.1 without (80,000 7.3 and 8.3; 40,000 2.6 either way).
+CLEAR_FROM = 8192
+
+
 class FnvRunner:
     def __init__(self, ctx: Context, path: str, offsets: np.ndarray, item_bytes: int = 4096,
                  wg_size: int = 256, device: str = "cuda", staging_bytes: int = 0):
@@ -42,6 +49,9 @@ class FnvRunner:
     def run(self, g="WI", o="strong", b="block", form=PLAIN, stream=None):
         """Launch, wait for the GPU and drain the host pool (every form stores
         both results of every item)."""
+        if self.n >= CLEAR_FROM:
+            with self.torch.cuda.stream(self.torch.cuda.ExternalStream(_stream(stream))):
+                self.out.fill_(-12345)
         self.launch(cell_code(g, o, b), form, stream)
         self.back.enqueue(stream)
         self.torch.cuda.synchronize()

@@ -24,7 +24,7 @@ def tmpdata(tmp_path_factory):
     shutil.rmtree(d, ignore_errors=True)
 
 
-POISON = -12345
+POISON = -54321
 
 
 def poison(runner):

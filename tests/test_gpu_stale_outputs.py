@@ -94,3 +94,26 @@ def test_every_cell_and_form_stores_every_item(gs, data, item, wg, n):
                                         "graph": g.GRAPH}[form])
             assert (ret == want_ret).all() and (f == want).all(), (form, cell)
     r.close()
+
+
+@pytest.mark.parametrize("n", [100, 8192, 70000])
+def test_large_runs_clear_their_results_first(gs, data, n):
+    """Runs whose launch is long clear the results before it (a short one's
+    time would show it)."""
+    g, ctx = gs
+    from conftest import POISON
+    from paper_1705_06965_amd.fnv import FnvRunner
+    import torch
+    r = FnvRunner(ctx, data, np.arange(n, dtype=np.uint64), 64, wg_size=64)
+    want = oracle.pread_fnv(data, np.arange(n, dtype=np.uint64), 64)
+    side = torch.cuda.Stream()
+    for s in (None, side):  # on the stream of the launch, so never after it
+        print("cleared", n, s, flush=True)
+        f, ret = r.run(stream=s)
+        assert (f == want[0]).all() and (ret == want[1]).all()
+    r.launch = lambda *a, **k: 0
+    for s in (None, side):
+        f, ret = r.run(stream=s)
+        left = -12345 if n >= 8192 else POISON
+        assert (ret == left).all() and (f.view(np.int64) == left).all()
+    r.close()
