@@ -97,4 +97,40 @@ constexpr uint32_t spread_group(uint64_t n, uint32_t item_bytes, uint32_t wg, ui
   return wg;
 }
 
+// Items that are in memory already, hashed by as many work-groups as they
+// fill: true if many lanes per item are ahead of the chains, which need 65,536
+// items to fill the chip.  The weights are cycles per byte and lane: a step
+// whose 8 KiB are all there 26, others 40 (not loaded ahead; also the bytes a
+// slot leaves empty are paid for), the chain 32.  Chains against many lanes:
+// 200,000 items of 640 bytes 51 against 75 us, of 4 KiB 244 against 233,
+// 65,536 of 8,256 bytes 174 against 281, 20,000 of them 133 against 91, 65,536
+// of 12 KiB 216 against 283, 40,000 of 16,448 bytes 262 against 243.
+inline bool consume_many_lanes(uint64_t n, uint32_t item_bytes) {
+  if (item_bytes <= kParMinItem) return false;
+  const uint64_t slot = item_bytes > kStepBytes ? kStepBytes : kSegBytes << par_lanes_log2(item_bytes);
+  const uint64_t whole = item_bytes / slot, part = item_bytes % slot ? 1 : 0;
+  const double par = (double)n * slot * (double)(whole * 26 + part * 40);
+  return par < 32.0 * item_bytes * (double)std::max<uint64_t>(n, 65536);
+}
+
+// The same with the caller's grid of work-groups of wg work-items: what counts
+// is how long a wavefront's share takes, by the wavefronts on a SIMD.  Chains
+// against many lanes, 20,000 items of 4 KiB: 79 work-groups of 256 66 against
+// 89 us, 313 of 64 66 against 84, 40 of 512 106 against 126, 20 of 1,024 (their
+// variant of many lanes spills) 185 against 323, 64 of 1,024 186 against 107;
+// 4,000 of 64 KiB in 4 of 1,024 2.9 against 4.6 ms, in 64 2.9 against 0.34.
+inline bool consume_many_lanes(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t grid,
+                               uint32_t cus) {
+  if (item_bytes <= kParMinItem || !cus) return false;
+  const uint64_t waves = (uint64_t)grid * (wg / 64);
+  const double per_simd = (double)(ceil_div(grid, cus) * wg) / 256;
+  const double chain_ns = per_simd <= 1 ? 15 : per_simd <= 2 ? 25 : 11.2 * per_simd;
+  const double step_ns = wg > kParBlock ? 2600 * std::max(per_simd, 4.0)
+                         : per_simd <= 1 ? 2650 : 1950 * std::max(per_simd, 2.0);
+  const double chain = (double)ceil_div(n, waves * 64) * item_bytes * chain_ns;
+  const double par = (double)(ceil_div(ceil_div(n, par_items(item_bytes)), waves) *
+                              par_steps(item_bytes)) * step_ns;
+  return par < chain;
+}
+
 }  // namespace gsys_k

@@ -427,14 +427,10 @@ int gsys_fnv4k_consume(gsys_ctx* ctx, uint64_t staging, uint64_t rets, uint64_t 
     return -EINVAL;
   void* args[] = {&staging, &rets, &n_items, &item_bytes, &out_fnv};
   hipStream_t s = (hipStream_t)stream;
-  // Many lanes per item, unless there are enough items for the serial chains
-  // to fill the chip (65,536 lanes' worth) and the items leave much of their
-  // lanes' bytes empty.  The weights are the measured costs per byte: dense
-  // items 26 cycles, others 40 (they are not loaded ahead), the chain 32.
-  const uint64_t slot = std::max<uint64_t>(item_bytes, (uint64_t)kSegBytes << par_lanes_log2(item_bytes));
-  const double par_cost = (double)n_items * slot * (slot == item_bytes ? 26 : 40);
-  const double serial_cost = 32.0 * item_bytes * (double)std::max<uint64_t>(n_items, 65536);
-  if (item_bytes > kParMinItem && par_cost < serial_cost) {
+  const bool par = grid ? consume_many_lanes(n_items, item_bytes, wg_size, grid,
+                                             gsys_internal::cu_count(ctx))
+                        : consume_many_lanes(n_items, item_bytes);
+  if (par) {
     // grid 0: four wavefronts per work-group, each with work, as many as run
     // at once; otherwise the caller's grid of wg_size work-items each
     const bool wide = grid && wg_size > kParBlock;

@@ -16,6 +16,10 @@ WRAPPER = """
 extern "C" int group_rule(uint64_t n, uint32_t item, uint32_t wg, uint32_t cus) {
   return gsys_k::many_lanes(n, item, wg, gsys_k::helped_block(wg, gsys_k::ceil_div(n, wg), cus));
 }
+extern "C" int consume_rule(uint64_t n, uint32_t item) { return gsys_k::consume_many_lanes(n, item); }
+extern "C" int consume_grid_rule(uint64_t n, uint32_t item, uint32_t wg, uint32_t grid, uint32_t cus) {
+  return gsys_k::consume_many_lanes(n, item, wg, grid, cus);
+}
 extern "C" int spread_rule(uint64_t n, uint32_t item, uint32_t wg, uint32_t cus, uint64_t slots) {
   return gsys_k::spread_group(n, item, wg, cus, slots);
 }
@@ -38,6 +42,8 @@ def rules(tmp_path_factory):
     assert b.returncode == 0, b.stderr
     lib = C.CDLL(so)
     lib.group_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32]
+    lib.consume_rule.argtypes = [C.c_uint64, C.c_uint32]
+    lib.consume_grid_rule.argtypes = [C.c_uint64] + [C.c_uint32] * 4
     lib.spread_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint64]
     lib.item_rule.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32]
     return lib
@@ -78,3 +84,21 @@ def test_work_item_calls_that_fill_the_chip(rules, n, wg, many):
     (20, 1 << 20, 64, 64, 8), (300, 256, 64, 65536, 64)])
 def test_spread_keeps_to_launches_that_fit_the_ring(rules, n, item, wg, slots, want):
     assert rules.spread_rule(n, item, wg, CUS, slots) == want
+
+
+@pytest.mark.parametrize("n,item,many", [
+    (50000, 4096, 1), (200000, 4096, 1), (60000, 8192, 1), (200, 1 << 20, 1), (200000, 640, 0),
+    (200000, 1024, 1), (65536, 8256, 0), (33000, 8256, 0), (20000, 8256, 1), (65536, 12288, 0),
+    (40000, 16448, 1), (40000, 24576, 1), (5000, 65600, 1), (200000, 512, 0)])
+def test_consume_counts_the_last_step(rules, n, item, many):
+    assert rules.consume_rule(n, item) == many
+
+
+@pytest.mark.parametrize("n,item,wg,grid,many", [
+    (20000, 4096, 256, 79, 0), (20000, 4096, 64, 313, 0), (20000, 4096, 512, 40, 0),
+    (20000, 4096, 1024, 5, 0), (20000, 4096, 1024, 20, 0), (20000, 4096, 1024, 64, 1),
+    (20000, 4096, 1024, 256, 1), (20000, 8256, 256, 79, 0), (4000, 65536, 1024, 64, 1),
+    (300, 65536, 256, 64, 1), (300, 65536, 256, 2, 1), (20000, 4096, 256, 200, 1),
+    (1000, 4096, 256, 64, 1), (20000, 4096, 256, 512, 1), (100, 512, 64, 2, 0)])
+def test_consume_with_a_grid(rules, n, item, wg, grid, many):
+    assert rules.consume_grid_rule(n, item, wg, grid, CUS) == many
