@@ -98,8 +98,9 @@ constexpr uint32_t spread_group(uint64_t n, uint32_t item_bytes, uint32_t wg, ui
 }
 
 // Items that are in memory already, hashed by as many work-groups as they
-// fill: true if many lanes per item are ahead of the chains, which need 65,536
-// items to fill the chip.  The weights are cycles per byte and lane: a step
+// fill: true if many lanes per item are ahead of the chains (where the items
+// are full: short ones go to the chains either way), which need 65,536 items
+// to fill the chip.  The weights are cycles per byte and lane: a step
 // whose 8 KiB are all there 26, others 40 (not loaded ahead; also the bytes a
 // slot leaves empty are paid for), the chain 32.  Chains against many lanes:
 // 200,000 items of 640 bytes 51 against 75 us, of 4 KiB 244 against 233,
@@ -113,20 +114,30 @@ inline bool consume_many_lanes(uint64_t n, uint32_t item_bytes) {
   return par < 32.0 * item_bytes * (double)std::max<uint64_t>(n, 65536);
 }
 
-// The same with the caller's grid of work-groups of wg work-items: what counts
-// is how long a wavefront's share takes, by the wavefronts on a SIMD.  Chains
-// against many lanes, 20,000 items of 4 KiB: 79 work-groups of 256 66 against
-// 89 us, 313 of 64 66 against 84, 40 of 512 106 against 126, 20 of 1,024 (their
-// variant of many lanes spills) 185 against 323, 64 of 1,024 186 against 107;
-// 4,000 of 64 KiB in 4 of 1,024 2.9 against 4.6 ms, in 64 2.9 against 0.34.
+// Groups of a wavefront of the many-lanes kernel, which keeps a bit for each of
+// at most 64.
+constexpr uint32_t kConsumeRounds = 64;
+constexpr uint64_t consume_rounds(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t grid) {
+  return ceil_div(n, (uint64_t)grid * (wg / 64) * par_items(item_bytes));
+}
+
+// The same with the caller's grid of work-groups of wg work-items (many lanes
+// make two of 512 out of one of 1,024): what counts is how long a wavefront's
+// share takes, by the wavefronts on a SIMD.  Chains against many lanes, 20,000
+// items of 4 KiB: 79 work-groups of 256 66 against 89 us, 200 66 against 40,
+// 313 of 64 66 against 84, 40 of 512 106 against 126; 300 of 64 KiB in 64 of
+// 256 966 against 38, 20,000 of 8,256 bytes in 79 of 256 132 against 400.
 inline bool consume_many_lanes(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t grid,
                                uint32_t cus) {
-  if (item_bytes <= kParMinItem || !cus) return false;
+  if (item_bytes <= kParMinItem || !cus ||
+      consume_rounds(n, item_bytes, wg, grid) > kConsumeRounds)
+    return false;
   const uint64_t waves = (uint64_t)grid * (wg / 64);
-  const double per_simd = (double)(ceil_div(grid, cus) * wg) / 256;
-  const double chain_ns = per_simd <= 1 ? 15 : per_simd <= 2 ? 25 : 11.2 * per_simd;
-  const double step_ns = wg > kParBlock ? 2600 * std::max(per_simd, 4.0)
-                         : per_simd <= 1 ? 2650 : 1950 * std::max(per_simd, 2.0);
+  const double chains = (double)(ceil_div(grid, cus) * wg) / 256;  // per SIMD
+  const double chain_ns = chains <= 1 ? 15 : chains <= 2 ? 25 : 11.2 * chains;
+  const uint32_t block = std::min(wg, kParBlock);
+  const double others = (double)(ceil_div((uint64_t)grid * (wg / block), cus) * block) / 256;
+  const double step_ns = others <= 1 ? 2650 : 1950 * std::max(others, 2.0);
   const double chain = (double)ceil_div(n, waves * 64) * item_bytes * chain_ns;
   const double par = (double)(ceil_div(ceil_div(n, par_items(item_bytes)), waves) *
                               par_steps(item_bytes)) * step_ns;

@@ -64,11 +64,11 @@ struct Tile {
 template <uint32_t WGMAX>
 constexpr uint32_t chunk_for() { return WGMAX <= 256 ? 256u : 128u; }
 
-// All 64 lanes of the wave call this.  Lane l hashes `nbytes` bytes of item
-// row0 + l * item_bytes.  `tile` is this wave's LDS tile (Tile<CH>::kBytes).
-template <uint32_t CH>
-__device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
-                                               uint32_t item_bytes, uint8_t* tile_generic) {
+// All 64 lanes of the wave call this.  Lane l hashes `nbytes` bytes of the item
+// at address row(l).  `tile` is this wave's LDS tile (Tile<CH>::kBytes).
+template <uint32_t CH, class Row>
+__device__ __forceinline__ uint64_t wave_fnv_rows(Row row, uint32_t nbytes, uint32_t item_bytes,
+                                                  uint8_t* tile_generic) {
   using T = Tile<CH>;
   lptr_t<uint8_t> tile = lp(tile_generic);
   const uint32_t lane = lane_id();
@@ -89,7 +89,7 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
       v[k] = u32x4{0, 0, 0, 0};
       // a row is read only where it holds bytes, inside its own item slot
       if (off < rlen[r] && off + col * 16 < item_bytes)
-        v[k] = ldg16(row0 + (uint64_t)r * item_bytes + off + col * 16);
+        v[k] = ldg16(row(r) + off + col * 16);
     }
   };
   if (maxlen) load(0);
@@ -101,27 +101,49 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
     }
     __builtin_amdgcn_wave_barrier();
     if (off + CH < maxlen) load(off + CH);  // prefetch the next step
-    lptr_t<const uint8_t> row = tile + lane * T::kRowStride;
-    if (off + CH <= nbytes) {
+    lptr_t<const uint8_t> mine = tile + lane * T::kRowStride;
+    if (__ballot(off < nbytes && off + CH > nbytes) == 0) {
+      if (off + CH <= nbytes) {
 #pragma unroll 2
-      for (uint32_t q = 0; q < CH / 16; ++q) {
-        const u32x4 w = *reinterpret_cast<lptr_t<const u32x4>>(row + q * 16);
+        for (uint32_t q = 0; q < CH / 16; ++q) {
+          const u32x4 w = *reinterpret_cast<lptr_t<const u32x4>>(mine + q * 16);
+          h = fnv_word4(h, w.x);
+          h = fnv_word4(h, w.y);
+          h = fnv_word4(h, w.z);
+          h = fnv_word4(h, w.w);
+        }
+      }
+    } else if (off < nbytes) {
+      // some lanes are at their items' ends: all go on in 16-byte pieces, and
+      // those take the rest of the last one byte by byte.  (With the others
+      // waiting for a byte-wise loop over all that is left, lengths up to 512
+      // took 60 ns a byte.)
+      const uint32_t left = min(CH, nbytes - off);
+      uint32_t q = 0;
+      for (; q + 16 <= left; q += 16) {
+        const u32x4 w = *reinterpret_cast<lptr_t<const u32x4>>(mine + q);
         h = fnv_word4(h, w.x);
         h = fnv_word4(h, w.y);
         h = fnv_word4(h, w.z);
         h = fnv_word4(h, w.w);
       }
-    } else if (off < nbytes) {
-      const uint32_t left = nbytes - off;
-      for (uint32_t q = 0; q < CH / 4 && q * 4 < left; ++q) {
-        const uint32_t w = *reinterpret_cast<lptr_t<const uint32_t>>(row + q * 4);
-        const int nb = (int)min(4u, left - q * 4);
-        h = fnv_word(h, w, nb);
+      if (q < left) {
+        const u32x4 w = *reinterpret_cast<lptr_t<const u32x4>>(mine + q);
+        for (uint32_t j = 0; q + j < left; ++j)
+          h = fnv_byte(h, (w[j >> 2] >> (8 * (j & 3u))) & 0xffu);
       }
     }
     __builtin_amdgcn_wave_barrier();
   }
   return h;
+}
+
+// The same for items that follow each other from row0 on.
+template <uint32_t CH>
+__device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
+                                               uint32_t item_bytes, uint8_t* tile) {
+  return wave_fnv_rows<CH>([=](uint32_t r) { return row0 + (uint64_t)r * item_bytes; }, nbytes,
+                           item_bytes, tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -262,10 +284,9 @@ __device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
 // The sum of the item's (x - s) p^(bytes to the end of its slot of 128 << ll
 // bytes in this step), in every lane of the item.  w: the lane's 128 bytes;
 // ent: low byte of the item's hash before the step; before: lanes holding
-// earlier bytes of the same item; wt(k): the weights' operand k.
-template <class Weights>
+// earlier bytes of the same item; wt: the weights.
 __device__ __forceinline__ uint64_t par_step(uint32_t (&w)[32], uint32_t ent, uint64_t before,
-                                             Weights wt, uint64_t colw, uint32_t ll) {
+                                             const i32x4 (&wt)[8], uint64_t colw, uint32_t ll) {
   // bytes to (t, r): byte c of b[t][r] is byte t of word 8 c + r
   uint32_t b[4][8];
 #pragma unroll
@@ -353,7 +374,7 @@ __device__ __forceinline__ uint64_t par_step(uint32_t (&w)[32], uint32_t ent, ui
         bx[q] = (int)x[t][4 * h + q];
         bs[q] = (int)(x[t][4 * h + q] ^ b[t][4 * h + q]);
       }
-      const i32x4 a = wt(2 * t + h);
+      const i32x4 a = wt[2 * t + h];
       dx = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bx, dx, 0, 0, 0);
       ds = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bs, ds, 0, 0, 0);
     }
@@ -380,20 +401,21 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
 }
 
-// All 64 lanes of the wavefront call this.  Hashes items first, first + 1, ...
-// of groups of par_items(item_bytes), a group every `stride` items, up to
-// `cnt`: item i's bytes start at row0 + i * item_bytes and it has len_of(i) of
-// them (at most item_bytes, a multiple of 16).  done(i, h) is called by one
-// lane per item.  `tile`: this wavefront's kParTile bytes of LDS.  kAhead: the
-// next step's bytes are loaded while this one is hashed and the weights stay
-// in registers (work-groups of up to 512 work-items; wider ones have half the
-// registers per lane and more wavefronts to hide the loads).
-template <bool kAhead, class LenOf, class Done>
+// All 64 lanes of the wavefront call this.  Hashes groups of
+// par_items(item_bytes) consecutive items: the first group's are from `first`
+// on, and after the one at i comes next(i)'s (the same in every lane), until
+// that is `cnt` or more; items from cnt on are not there.  Item i's bytes start
+// at row0 + i * item_bytes and it has len_of(i) of them (at most item_bytes, a
+// multiple of 16); len0 is the length of item first + lane, in the lanes below
+// par_items.  done(i, h) is called by one lane per item.  `tile`: this
+// wavefront's kParTile bytes of LDS.  The next step's bytes are loaded while
+// this one is hashed, and the weights stay in registers (256 per lane, so
+// work-groups of up to 512 work-items).
+template <class LenOf, class Next, class Done>
 __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes, uint64_t first,
-                                             uint64_t stride, uint64_t cnt, uint8_t* tile_generic,
-                                             LenOf len_of, Done done) {
+                                             uint32_t len0, uint64_t cnt, uint8_t* tile_generic,
+                                             LenOf len_of, Next next, Done done) {
   first = uniform64(first);
-  stride = uniform64(stride);
   cnt = uniform64(cnt);
   row0 = uniform64(row0);
   if (first >= cnt) return;
@@ -412,21 +434,15 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
   const uint64_t colw = fnv_w.col[(16u >> (6 - ll)) - 1u - col];
   const uint64_t slotw = fnv_w.seg[ll];
   const uint64_t wbase = (uint64_t)&fnv_w.a[0][lane][0];
-  i32x4 held[8];
-  if constexpr (kAhead) {
+  i32x4 wt[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) held[k] = *gp<const i32x4>(wbase + k * sizeof fnv_w.a[0]);
-  }
-  auto wt = [&](int k) -> i32x4 {
-    if constexpr (kAhead) return held[k];
-    uint64_t a = wbase + k * sizeof fnv_w.a[0];
-    asm("" : "+v"(a));  // loaded where it is used
-    return *gp<const i32x4>(a);
-  };
+  for (int k = 0; k < 8; ++k) wt[k] = *gp<const i32x4>(wbase + k * sizeof fnv_w.a[0]);
   auto set_len = [&](uint32_t buf, uint64_t i0) {
     if (lane < items) rlen[16 * buf + lane] = i0 + lane < cnt ? len_of(i0 + lane) : 0u;
     __builtin_amdgcn_wave_barrier();
   };
+  if (lane < items) rlen[lane] = first + lane < cnt ? len0 : 0u;
+  __builtin_amdgcn_wave_barrier();
   // Load k covers 1 KiB: part of one item, or two items' 512-byte slots.  A
   // lane's place in it does not depend on k; the rest is the same in every
   // lane.
@@ -478,13 +494,13 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
     }
   };
   uint32_t buf = 0;
-  set_len(0, first);
   bool have = false;  // v holds the coming step's bytes
-  for (uint64_t i0 = first; i0 < cnt; i0 += stride) {
+  for (uint64_t i0 = first, i1; i0 < cnt; i0 = i1) {
+    i1 = next(i0);
     const uint32_t len = rlen[16 * buf + (seg >> ll)];
     uint32_t steps = 1;
     if (ll == 6) steps = max(1u, (__builtin_amdgcn_readfirstlane(len) + kStepBytes - 1) / kStepBytes);
-    const bool more = i0 + stride < cnt;
+    const bool more = i1 < cnt;
     uint64_t h = kFnvBasis;
     for (uint32_t st = 0; st < steps; ++st) {
       if (!have) {
@@ -499,11 +515,9 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
       }
       __builtin_amdgcn_wave_barrier();
       const bool same = st + 1 < steps;
-      if (!same && more) set_len(buf ^ 1u, i0 + stride);
-      if constexpr (kAhead) {
-        have = (same || more) && whole(same ? buf : buf ^ 1u, same ? st + 1 : 0u);
-        if (have) load_whole(same ? i0 : i0 + stride, same ? st + 1 : 0u);
-      }
+      if (!same && more) set_len(buf ^ 1u, i1);
+      have = (same || more) && whole(same ? buf : buf ^ 1u, same ? st + 1 : 0u);
+      if (have) load_whole(same ? i0 : i1, same ? st + 1 : 0u);
       uint32_t w[32];
 #pragma unroll
       for (uint32_t q = 0; q < 8; ++q) {
@@ -525,6 +539,19 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
     if ((seg & ((1u << ll) - 1u)) == 0 && it < cnt) done(it, h);
     buf ^= 1u;
   }
+}
+
+// The same, a group every `stride` items.
+template <class LenOf, class Done>
+__device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes, uint64_t first,
+                                             uint64_t stride, uint64_t cnt, uint8_t* tile,
+                                             LenOf len_of, Done done) {
+  first = uniform64(first);
+  stride = uniform64(stride);
+  const uint64_t i = first + lane_id();
+  const uint32_t len0 = lane_id() < par_items(item_bytes) && i < cnt ? len_of(i) : 0u;
+  wave_fnv_par(
+      row0, item_bytes, first, len0, cnt, tile, len_of, [=](uint64_t i) { return i + stride; }, done);
 }
 
 }  // namespace gsys_k

@@ -85,7 +85,7 @@ __device__ __forceinline__ void consume_items(const FnvArgs& A, uint64_t first, 
       hi = min(cnt, lo + 64);
       step = items;
     }
-    wave_fnv_par<true>(
+    wave_fnv_par(
         row0, A.item_bytes, lo, step, hi, lds + wave * kParTile,
         [&](uint64_t i) { return lens[i]; },
         [&](uint64_t i, uint64_t h) { A.out_fnv[first + i] = h; });
@@ -234,23 +234,144 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_consume(
   }
 }
 
-// The same for items of more than 512 bytes: the launch's wavefronts take
-// par_items() items at a time.
-template <uint32_t WGMAX>
-__global__ __launch_bounds__(WGMAX, WGMAX <= kParBlock ? 2 : 4) void fnv4k_consume_par(
-    uint64_t staging, const int64_t* rets, uint64_t n_items, uint32_t item_bytes,
-    uint64_t* out_fnv) {
+// The same for items of more than 512 bytes, mostly by many lanes each.  A
+// step costs the same however short its items are, so short items are hashed by
+// the chains.
+//
+// A wavefront takes a group of par_items items per round, at the stride of the
+// launch.  First it looks at the lengths of its own items, 64 at a time: one
+// load, which brings the first group's lengths too, and nothing to exchange
+// with others.  Chains take one lane per item, so those 64 need not follow
+// each other; and since every wavefront's items come from all over the launch,
+// a region of short ones leaves none idle.  (With consecutive items for each
+// wavefront the steps took 3 us longer: fewer memory channels at a time.)
+//
+// us for slots of 4 KiB in HBM, by the chains alone, many lanes alone, and
+// this: 50,000 full 71, 60.4, 61.0; lengths up to 4,096 255, 77, 79; up to
+// 1,000 75, 72, 41; up to 512 39, 72, 24; up to 100 9.9, 71, 8.3; half of them
+// 0 69, 65, 67.  200,000 full 246, 232, 236; up to 4,096 583, 298, 255; up to
+// 512 81, 277, 45; ascending lengths 141, 297, 212.
+// LDS of a wavefront, for either way.
+constexpr uint32_t kConsumeTile = std::max(kParTile, Tile<128>::kBytes);
+
+struct ConsumeArgs {
+  uint64_t staging;
+  const int64_t* rets;
+  uint64_t n_items;
+  uint64_t* out_fnv;
+  uint32_t item_bytes;
+};
+
+// A reduction over the lanes (0 must be its identity).
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op) {
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr 1
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast 15
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast 31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  return wave_reduce(v, [](uint32_t a, uint32_t b) { return max(a, b); });
+}
+
+// Which of the up to 64 items of a look the chains hash, as a bit per group
+// (the same in every lane).  `groups` of them hold items; len is the length of
+// this lane's item (0 if there is none), part the lanes whose item is not full.
+// Either all, or the groups whose items have at most 512 bytes, or none.
+//
+// Costs in ns, with two wavefronts on a SIMD: a step of a group, half as much
+// again where not all of it is there; a byte of the chains while all items
+// that are not empty go on, and once some have ended.
+__device__ __forceinline__ uint64_t chain_groups(uint32_t item_bytes, uint32_t groups, uint32_t len,
+                                                 uint64_t part) {
+  constexpr uint32_t kStep = 3900, kAll = 25, kSome = 45;
+  const uint32_t ilog = 6 - par_lanes_log2(item_bytes), lane = lane_id();
+  const uint32_t most = wave_max(len);
+  const uint32_t least = min(~wave_max(len ? ~len : 0u), most) & ~255u;
+  uint32_t steps = groups;
+  if (ilog == 0 && most > kStepBytes)
+    steps = wave_reduce(lane < groups ? max(1u, (len + kStepBytes - 1) / kStepBytes) : 0u,
+                        [](uint32_t a, uint32_t b) { return a + b; });
+  const uint32_t ragged = min(steps, (uint32_t)__popcll(part));
+  if (kAll * least + kSome * (most - least) < kStep * steps + kStep / 2 * ragged) return ~0ull;
+  // lanes with longer items, then groups with any
+  uint64_t big = __ballot(len > kParMinItem);
+  for (uint32_t k = 0; k < ilog; ++k) big |= big >> (1u << k);
+  const uint64_t small = __ballot(lane < groups && !((big >> (lane << ilog)) & 1ull));
+  const uint32_t top = wave_max((small >> (lane >> ilog)) & 1ull ? len : 0u);
+  return kSome * top < (kStep + kStep / 2) * (uint32_t)__popcll(small) ? small : 0ull;
+}
+
+__global__ __launch_bounds__(kParBlock, 2) void fnv4k_consume_par(ConsumeArgs A) {
   extern __shared__ __align__(16) uint8_t lds[];
-  const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  const uint32_t items = par_items(item_bytes);
-  wave_fnv_par<(WGMAX <= kParBlock)>(
-      staging, item_bytes, ((uint64_t)blockIdx.x * waves + wave) * items,
-      (uint64_t)gridDim.x * waves * items, n_items, lds + wave * kParTile,
-      [&](uint64_t i) {
-        const int64_t r = rets[i];
-        return r > 0 ? (uint32_t)min<int64_t>(r, (int64_t)item_bytes) : 0u;
+  const uint32_t lane = lane_id();
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t ilog = 6 - par_lanes_log2(A.item_bytes), items = 1u << ilog;
+  const uint64_t first = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) << ilog;
+  const uint64_t step = ((uint64_t)gridDim.x * (blockDim.x >> 6)) << ilog;
+  uint8_t* tile = lds + wave * kConsumeTile;
+  auto len_of = [&](uint64_t i) {
+    const int64_t r = A.rets[i];
+    return r > 0 ? (uint32_t)min<int64_t>(r, (int64_t)A.item_bytes) : 0u;
+  };
+  auto len_or_0 = [&](uint64_t i) { return i < A.n_items ? len_of(i) : 0u; };
+  auto store = [&](uint64_t i, uint64_t h) { A.out_fnv[i] = h; };
+  // A look is at 64 >> ilog rounds; lane l has item l mod `items` of the
+  // l >> ilog-th of them.  (The launch has at most kConsumeRounds.)
+  uint64_t many = 0;  // bit j: many lanes hash the group of round j
+  bool chained = false;
+  uint64_t i = first + (uint64_t)(lane >> ilog) * step + (lane & (items - 1u));
+  uint32_t coming = len_or_0(i);
+  const uint32_t len0 = coming;  // (the first group's in the first lanes)
+  uint32_t round = 0;
+  for (uint64_t g0 = first; g0 < A.n_items; g0 += step << (6 - ilog), round += 64u >> ilog) {
+    const uint64_t at = i;
+    const bool there = at < A.n_items;
+    const uint32_t len = coming;
+    i += step << (6 - ilog);
+    coming = len_or_0(i);
+    const uint64_t part = __ballot(there && len < A.item_bytes);
+    // groups that hold items: those whose first one is there
+    const uint64_t has = __ballot(lane < (64u >> ilog) && g0 + lane * step < A.n_items);
+    uint64_t chains = 0;
+    if (__builtin_expect(part != 0, 0))
+      chains = chain_groups(A.item_bytes, (uint32_t)__popcll(has), len, part);
+    if (__builtin_expect(chains != 0, 0)) {
+      const bool mine = there && ((chains >> (lane >> ilog)) & 1ull);
+      const uint64_t g = A.staging + g0 * A.item_bytes;
+      const uint64_t h = wave_fnv_rows<128>(
+          [&](uint32_t r) {
+            return g + ((uint64_t)(r >> ilog) * step + (r & (items - 1u))) * A.item_bytes;
+          },
+          mine ? len : 0u, A.item_bytes, tile);
+      if (mine) store(at, h);
+      chained = true;
+    }
+    many |= (has & ~chains) << round;
+  }
+  if (__builtin_expect(!chained, 1)) {
+    wave_fnv_par(A.staging, A.item_bytes, first, len0, A.n_items, tile, len_of,
+                 [&](uint64_t i) { return i + step; }, store);
+    return;
+  }
+  many = uniform64(many);
+  if (!many) return;
+  const uint32_t skip = (uint32_t)__builtin_ctzll(many);
+  const uint64_t begin = first + skip * step;
+  many >>= skip;
+  wave_fnv_par(
+      A.staging, A.item_bytes, begin, len_or_0(begin + lane), A.n_items, tile, len_of,
+      [&](uint64_t i) -> uint64_t {  // bit 0 of `many` is i's round
+        many >>= 1;
+        if (!many) return A.n_items;
+        const uint32_t s = (uint32_t)__builtin_ctzll(many);
+        many >>= s;
+        return i + (s + 1) * step;
       },
-      [&](uint64_t i, uint64_t h) { out_fnv[i] = h; });
+      store);
 }
 
 __global__ void zero_words(unsigned long long* p, uint32_t n) {
@@ -425,29 +546,34 @@ int gsys_fnv4k_consume(gsys_ctx* ctx, uint64_t staging, uint64_t rets, uint64_t 
   if (item_bytes == 0 || item_bytes % 64 || item_bytes > (1u << 20)) return -EINVAL;
   if (!(wg_size == 64 || wg_size == 128 || wg_size == 256 || wg_size == 512 || wg_size == 1024))
     return -EINVAL;
-  void* args[] = {&staging, &rets, &n_items, &item_bytes, &out_fnv};
   hipStream_t s = (hipStream_t)stream;
-  const bool par = grid ? consume_many_lanes(n_items, item_bytes, wg_size, grid,
-                                             gsys_internal::cu_count(ctx))
-                        : consume_many_lanes(n_items, item_bytes);
-  if (par) {
+  const uint32_t cus = gsys_internal::cu_count(ctx);
+  const bool many = grid ? consume_many_lanes(n_items, item_bytes, wg_size, grid, cus)
+                         : consume_many_lanes(n_items, item_bytes);
+  if (many) {
     // grid 0: four wavefronts per work-group, each with work, as many as run
-    // at once; otherwise the caller's grid of wg_size work-items each
-    const bool wide = grid && wg_size > kParBlock;
-    const uint32_t block = grid ? wg_size : 256;
-    const uint32_t lds = (block / 64) * kParTile;
-    const void* k = wide ? (const void*)fnv4k_consume_par<1024>
-                         : (const void*)fnv4k_consume_par<kParBlock>;
-    const uint64_t per = (uint64_t)(block / 64) * par_items(item_bytes);
-    const uint64_t nb = (n_items + per - 1) / per;
+    // at once; otherwise the caller's grid of wg_size work-items each, two
+    // work-groups of 512 for one of 1,024 (whose registers are too few)
+    if (gsys_internal::no_device(ctx)) return -ENODEV;
+    const uint32_t block = grid ? std::min(wg_size, kParBlock) : 256;
+    const uint64_t blocks = (uint64_t)grid * (wg_size / block);
+    const uint32_t lds = (block / 64) * kConsumeTile;
+    const void* k = (const void*)fnv4k_consume_par;
+    const uint64_t nb = ceil_div(n_items, (uint64_t)(block / 64) * par_items(item_bytes));
     if (!grid) {
-      if (gsys_internal::no_device(ctx)) return -ENODEV;
       grid = gsys_internal::resident_grid(ctx, k, block, lds);
       if (!grid) return -ENODEV;
+      grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(grid, ceil_div(nb, kConsumeRounds)),
+                                          0x7fffffffu);
+    } else {
+      grid = (uint32_t)std::min<uint64_t>(blocks, 0x7fffffffu);
     }
     if (grid > nb) grid = (uint32_t)nb;
+    ConsumeArgs A{staging, (const int64_t*)rets, n_items, (uint64_t*)out_fnv, item_bytes};
+    void* args[] = {&A};
     return gsys_internal::launch(ctx, k, grid, block, lds, args, s);
   }
+  void* args[] = {&staging, &rets, &n_items, &item_bytes, &out_fnv};
   const uint64_t nb = (n_items + wg_size - 1) / wg_size;
   if (!grid || grid > nb) grid = (uint32_t)std::min<uint64_t>(nb, 0x7fffffffull);
   const bool small = wg_size <= 256;

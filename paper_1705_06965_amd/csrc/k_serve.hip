@@ -133,7 +133,7 @@ __device__ int64_t scan_range(const SvArgs& A, int32_t fd, uint64_t off, uint64_
       if (threadIdx.x < cnt) A.digests[dig0 + blk0 + threadIdx.x] = h;
     } else {
       const uint32_t items = par_items(kBlock);
-      wave_fnv_par<true>(
+      wave_fnv_par(
           base, kBlock, wave * items, (kWG / 64) * items, cnt, lds + wave * kParTile,
           [&](uint64_t i) { return bytes_of((uint32_t)i); },
           [&](uint64_t i, uint64_t h) { A.digests[dig0 + blk0 + i] = h; });

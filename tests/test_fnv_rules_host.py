@@ -96,7 +96,7 @@ def test_consume_counts_the_last_step(rules, n, item, many):
 
 @pytest.mark.parametrize("n,item,wg,grid,many", [
     (20000, 4096, 256, 79, 0), (20000, 4096, 64, 313, 0), (20000, 4096, 512, 40, 0),
-    (20000, 4096, 1024, 5, 0), (20000, 4096, 1024, 20, 0), (20000, 4096, 1024, 64, 1),
+    (20000, 4096, 1024, 5, 0), (20000, 4096, 1024, 20, 1), (20000, 4096, 1024, 64, 1),
     (20000, 4096, 1024, 256, 1), (20000, 8256, 256, 79, 0), (4000, 65536, 1024, 64, 1),
     (300, 65536, 256, 64, 1), (300, 65536, 256, 2, 1), (20000, 4096, 256, 200, 1),
     (1000, 4096, 256, 64, 1), (20000, 4096, 256, 512, 1), (100, 512, 64, 2, 0)])
