@@ -20,10 +20,10 @@ constexpr uint32_t kParMinItem = 512;
 // lane).
 constexpr uint32_t kParBlock = 512;
 
-// Lanes an item occupies in a step (a power of two of at least one matrix
-// column, at most the wavefront) as a shift.
+// Lanes an item of more than kParMinItem bytes occupies in a step (a power of
+// two, at most the wavefront) as a shift.
 constexpr uint32_t par_lanes_log2(uint32_t item_bytes) {
-  uint32_t k = 2;
+  uint32_t k = 3;
   while (k < 6 && (kSegBytes << k) < item_bytes) ++k;
   return k;
 }

@@ -179,7 +179,7 @@ constexpr uint64_t kFnvBasis = 0xcbf29ce484222325ull;
 constexpr uint32_t kColBytes = 4 * kSegBytes;     // summed by one MFMA column
 constexpr uint32_t kSegStride = kSegBytes + 16;   // in LDS: conflict-free 16-byte reads
 // Wave tile: the step's bytes, then the byte counts of two groups of items.
-constexpr uint32_t kParTile = 64 * kSegStride + 2 * 16 * 4;
+constexpr uint32_t kParTile = 64 * kSegStride + 2 * 8 * 4;
 
 struct FnvWeights {
   // [t * 2 + half][lane][register]: four digits of one plane per register
@@ -388,7 +388,7 @@ __device__ __forceinline__ uint64_t par_step(uint32_t (&w)[32], uint32_t ent, ui
   sum *= colw;
   sum += shfl_xor64(sum, 16);
   sum += shfl_xor64(sum, 32);
-  if (ll > 2) sum += dpp64<0xb1>(sum);   // lane ^ 1
+  sum += dpp64<0xb1>(sum);               // lane ^ 1
   if (ll > 3) sum += dpp64<0x4e>(sum);   // lane ^ 2
   if (ll > 4) sum += dpp64<0x141>(sum);  // the other four of eight
   if (ll > 5) sum += dpp64<0x140>(sum);  // the other eight of sixteen
@@ -406,11 +406,11 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 // on, and after the one at i comes next(i)'s (the same in every lane), until
 // that is `cnt` or more; items from cnt on are not there.  Item i's bytes start
 // at row0 + i * item_bytes and it has len_of(i) of them (at most item_bytes, a
-// multiple of 16); len0 is the length of item first + lane, in the lanes below
-// par_items.  done(i, h) is called by one lane per item.  `tile`: this
-// wavefront's kParTile bytes of LDS.  The next step's bytes are loaded while
-// this one is hashed, and the weights stay in registers (256 per lane, so
-// work-groups of up to 512 work-items).
+// multiple of 16 and more than kParMinItem); len0 is the length of item first +
+// lane, in the lanes below par_items.  done(i, h) is called by one lane per
+// item.  `tile`: this wavefront's kParTile bytes of LDS.  The next step's bytes
+// are loaded while this one is hashed, and the weights stay in registers (256
+// per lane, so work-groups of up to 512 work-items).
 template <class LenOf, class Next, class Done>
 __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes, uint64_t first,
                                              uint32_t len0, uint64_t cnt, uint8_t* tile_generic,
@@ -438,23 +438,20 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
 #pragma unroll
   for (int k = 0; k < 8; ++k) wt[k] = *gp<const i32x4>(wbase + k * sizeof fnv_w.a[0]);
   auto set_len = [&](uint32_t buf, uint64_t i0) {
-    if (lane < items) rlen[16 * buf + lane] = i0 + lane < cnt ? len_of(i0 + lane) : 0u;
+    if (lane < items) rlen[8 * buf + lane] = i0 + lane < cnt ? len_of(i0 + lane) : 0u;
     __builtin_amdgcn_wave_barrier();
   };
   if (lane < items) rlen[lane] = first + lane < cnt ? len0 : 0u;
   __builtin_amdgcn_wave_barrier();
-  // Load k covers 1 KiB: part of one item, or two items' 512-byte slots.  A
-  // lane's place in it does not depend on k; the rest is the same in every
-  // lane.
-  const uint32_t two = ll == 2 ? lane >> 5 : 0u;
-  const uint32_t at = (lane * 16) & ((kSegBytes << ll) - 1u);
-  const uint32_t lane_off = two * item_bytes + at;
-  auto item_of = [&](uint32_t k) { return ll == 2 ? 2 * k : k >> (ll - 3); };
-  auto off_of = [&](uint32_t k) { return ll == 2 ? 0u : (k & ((1u << (ll - 3)) - 1u)) * 1024u; };
+  // Load k covers 1 KiB of one item.  A lane's place in it does not depend on
+  // k; the rest is the same in every lane.
+  const uint32_t at = lane * 16;
+  auto item_of = [&](uint32_t k) { return k >> (ll - 3); };
+  auto off_of = [&](uint32_t k) { return (k & ((1u << (ll - 3)) - 1u)) * 1024u; };
   u32x4 v[8];
   // bytes of the lane's item from the vector of load k on (<= 0: none)
   auto left = [&](uint32_t k, uint32_t buf, uint32_t step) {
-    return (int32_t)(rlen[16 * buf + item_of(k) + two] - step * kStepBytes - off_of(k) - at);
+    return (int32_t)(rlen[8 * buf + item_of(k)] - step * kStepBytes - off_of(k) - at);
   };
   // 16 bytes at a scalar address plus a 32-bit offset of the lane (opaque, so
   // that no 64-bit address per load is kept in vector registers)
@@ -467,7 +464,7 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
   auto whole = [&](uint32_t buf, uint32_t step) {
     if (ll < 6 && item_bytes != kSegBytes << ll) return false;
     const uint32_t need = ll == 6 ? (step + 1) * kStepBytes : item_bytes;
-    return __ballot(rlen[16 * buf + (lane & (items - 1u))] < need) == 0;
+    return __ballot(rlen[8 * buf + (lane & (items - 1u))] < need) == 0;
   };
   auto load_whole = [&](uint64_t i0, uint32_t step) {
     const uint64_t p = row0 + i0 * item_bytes + step * kStepBytes;
@@ -481,7 +478,7 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
     for (uint32_t k = 0; k < 8; ++k) {
       v[k] = u32x4{0, 0, 0, 0};
       if (left(k, buf, step) > 0)
-        v[k] = fetch(row0 + (i0 + item_of(k)) * item_bytes + step * kStepBytes + off_of(k), lane_off);
+        v[k] = fetch(row0 + (i0 + item_of(k)) * item_bytes + step * kStepBytes + off_of(k), at);
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
@@ -497,7 +494,7 @@ __device__ __forceinline__ void wave_fnv_par(uint64_t row0, uint32_t item_bytes,
   bool have = false;  // v holds the coming step's bytes
   for (uint64_t i0 = first, i1; i0 < cnt; i0 = i1) {
     i1 = next(i0);
-    const uint32_t len = rlen[16 * buf + (seg >> ll)];
+    const uint32_t len = rlen[8 * buf + (seg >> ll)];
     uint32_t steps = 1;
     if (ll == 6) steps = max(1u, (__builtin_amdgcn_readfirstlane(len) + kStepBytes - 1) / kStepBytes);
     const bool more = i1 < cnt;
