@@ -307,8 +307,9 @@ const char *gsys_strerror(int code);
  *   form      GSYS_PLAIN (grid n_items / wg_size) or GSYS_PERSISTENT /
  *             GSYS_GRAPH (co-resident grid looping over batches of at most
  *             wg_size items, double-buffered non-blocking group calls; a
- *             batch is one list call of at most 256 items and 256 KiB, shorter
- *             when there are few items; cell ignored).
+ *             batch is one list call of at most 256 items and 256 KiB, or of a
+ *             single item where that is larger, shorter when there are few
+ *             items; cell ignored).
  *             The persistent grid is 64 work-groups (fewer if fewer are
  *             resident or there are fewer batches; environment
  *             GSYS_PERSISTENT_GRID sets it instead): every work-group waiting
@@ -593,7 +594,7 @@ int gsys_canary(gsys_ctx *ctx, int fd, uint64_t buf, uint64_t n_items, uint64_t 
  * progress not registered), -ENODEV.
  */
 /* Bytes of one piece buffer of gsys_wordcount_open for reads of `chunk`
- * bytes: the carried bytes, the piece and the scanner's window past it. */
+ * bytes: the carried bytes, the piece and room past it. */
 uint64_t gsys_wordcount_open_buffer_bytes(uint32_t chunk);
 /* Work-groups that gsys_wordcount_open launches at most in this context:
  * staging and progress records for more are not used. */
@@ -687,7 +688,8 @@ int gsys_file_kernel_io(gsys_ctx *ctx, int fd, uint32_t nr, uint64_t data, uint6
  * out_fnv[i] = FNV-1a-64 of the first rets[i] bytes (rets: device int64[n],
  * values <= 0 hash nothing) of staging + i * item_bytes.  grid 0 = as many
  * work-groups as the items fill, otherwise a grid-stride loop of `grid`
- * work-groups of wg_size work-items over them.
+ * work-groups of wg_size work-items over them (a work-group of 1,024 may run as
+ * two of 512).
  * n_items == 0 returns 0 at once (the pointers may then be null).
  * Errors: -EINVAL.
  */

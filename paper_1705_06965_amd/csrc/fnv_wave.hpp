@@ -167,10 +167,10 @@ __device__ __forceinline__ uint64_t wave_fnv_t(uint64_t row0, uint32_t nbytes,
 // 512 bytes.  Bytes past an item's end are zeros: a zero byte multiplies h by
 // p, which the inverse of p undoes.
 //
-// Bound by vector-ALU issue: 781 instructions and 16 MFMAs per 8 KiB step of
+// Bound by vector-ALU issue: about 780 instructions and 16 MFMAs per 8 KiB step of
 // a wavefront (26 cycles per byte and lane; the serial chain takes 32), but a
 // 4 KiB item takes half a step instead of the chain's 61 us.  Measured: 50,000
-// items of 4 KiB in HBM 106 -> 59 us (3.5 TB/s), 180 of 1 MiB 15.4 -> 0.27 ms,
+// items of 4 KiB in HBM 106 -> 60 us (3.4 TB/s), 200 of 1 MiB 15.4 -> 0.27 ms,
 // a kernel that reads 64 of 4 KiB by one list call and hashes them in one
 // work-group of eight wavefronts 85 -> 42 us.
 

@@ -247,10 +247,10 @@ __global__ __launch_bounds__(WGMAX, WGMAX <= 256 ? 2 : 4) void fnv4k_consume(
 // wavefront the steps took 3 us longer: fewer memory channels at a time.)
 //
 // us for slots of 4 KiB in HBM, by the chains alone, many lanes alone, and
-// this: 50,000 full 71, 60.4, 61.0; lengths up to 4,096 255, 77, 79; up to
-// 1,000 75, 72, 41; up to 512 39, 72, 24; up to 100 9.9, 71, 8.3; half of them
-// 0 69, 65, 67.  200,000 full 246, 232, 236; up to 4,096 583, 298, 255; up to
-// 512 81, 277, 45; ascending lengths 141, 297, 212.
+// this: 50,000 full 71, 60.5, 60.8; lengths up to 4,096 255, 78, 79; up to
+// 1,000 74, 72, 40; up to 512 39, 72, 24; up to 100 9.8, 72, 8.2; half of them
+// 0 68, 65, 66.  200,000 full 246, 242, 241; up to 4,096 582, 302, 257; up to
+// 512 81, 277, 44; ascending lengths 148, 300, 212.
 // LDS of a wavefront, for either way.
 constexpr uint32_t kConsumeTile = std::max(kParTile, Tile<128>::kBytes);
 
@@ -435,11 +435,12 @@ int gsys_fnv4k(gsys_ctx* ctx, int fd, uint64_t offsets, uint64_t n_items, uint32
   };
 
   if (form == GSYS_PERSISTENT || form == GSYS_GRAPH) {
-    // Lists of at most 256 items and 256 KiB: one service thread runs a list,
-    // so the first bytes cross the link a list's service time after the start
-    // and the last list is hashed after the link is done.  A launch of few
-    // items takes shorter ones still, at least 128 (two per work-group of the
-    // default grid) so that every service thread has several, down to 64 KiB.
+    // Lists of at most 256 items and 256 KiB, or of one larger item: one
+    // service thread runs a list, so the first bytes cross the link a list's
+    // service time after the start and the last list is hashed after the link
+    // is done.  A launch of few items takes shorter ones still, at least 128
+    // (two per work-group of the default grid) so that every service thread has
+    // several, down to 64 KiB.
     // End to end (with a drain about 40 us longer than today's), 1 GiB in 4 KiB
     // items: 20.2 ms with 1 MiB lists, 20.1 with 512 KiB, 19.9 with 256 KiB,
     // 20.0 with 128 KiB; 5,003 items: 585 us with 1 MiB, 495 with 256 KiB, 485

@@ -504,7 +504,10 @@ __global__ __launch_bounds__(WG) void wordscan_plain(WsArgs A) {
 // at kOpenHead - 17, each piece's data on a fresh 64-byte line.
 
 constexpr uint32_t kOpenHead = 64;
-constexpr uint32_t kOpenTail = (32u << 10) + 48;  // room past the piece
+// Room past the piece.  A scan reads at most the rest of the last 16-byte
+// vector; callers size their buffers by the whole, which decides what is
+// accepted and how many work-groups fit, so it stays.
+constexpr uint32_t kOpenTail = (32u << 10) + 48;
 constexpr uint32_t kCarry = kOverlap;  // deferred bytes
 
 struct WoArgs {
@@ -725,7 +728,7 @@ int gsys_wordcount_open(gsys_ctx* ctx, int dirfd, uint64_t paths, uint32_t nfile
   if (!nfiles) return 0;  // the outputs are empty and may be null
   if (!queries || !qlens || !counts || !file_ret) return -EINVAL;
   if (gsys_internal::check_host_range(ctx, paths, (uint64_t)nfiles * GSYS_PATH_MAX)) return -EFAULT;
-  // carry head + data + the scanner's window past the last valid byte
+  // carry head + data + the room past it
   const uint32_t cbuf = (uint32_t)gsys_wordcount_open_buffer_bytes(chunk);
   const uint64_t per_wg = 2ull * cbuf;
   if (staging_bytes < per_wg) return -EINVAL;
