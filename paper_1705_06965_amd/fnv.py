@@ -11,11 +11,13 @@ from . import (Context, FD_READ, PLAIN, PERSISTENT, GRAPH, Readback, check, lib,
                _stream)
 
 
-# Runs of this many items clear the results first.  The kernel that does it
-# costs 3 us, and a launch of more calls than the ring has slots is faster after
-# one, whatever it does: the work-item calls of 200,000 items of 1 KiB take 21.0
-# ms, 23.1 without (80,000 7.3 and 8.3; 40,000 2.6 either way).
-CLEAR_FROM = 8192
+# Plain launches of this many work-item calls, more than a ring of 65,536 slots
+# has, clear the results first: they are faster after another kernel, whatever
+# it does.  100,000 items of 576 bytes in work-groups of 1,024 take 10.9 ms, 13.2
+# without; of 4 KiB in 64 18.1 and 20.0; 200,000 of 1 KiB in 256 21.3 and 23.9;
+# 40,000 2.6 either way.  Not through a switched stream where torch's current one
+# is the launch's: that costs 0.2 ms and the gain.
+CLEAR_FROM = 65537
 
 
 class FnvRunner:
@@ -46,12 +48,19 @@ class FnvRunner:
                                     self.out_fnv.data_ptr(), self.out_ret.data_ptr(), cell, form,
                                     self.wg_size, _stream(stream)), "gsys_fnv4k")
 
+    def _clear(self, stream):
+        cuda, s = self.torch.cuda, _stream(stream)
+        if s == cuda.current_stream().cuda_stream:
+            self.out.fill_(-12345)
+            return
+        with cuda.stream(cuda.ExternalStream(s)):
+            self.out.fill_(-12345)
+
     def run(self, g="WI", o="strong", b="block", form=PLAIN, stream=None):
         """Launch, wait for the GPU and drain the host pool (every form stores
         both results of every item)."""
-        if self.n >= CLEAR_FROM:
-            with self.torch.cuda.stream(self.torch.cuda.ExternalStream(_stream(stream))):
-                self.out.fill_(-12345)
+        if self.n >= CLEAR_FROM and form == PLAIN and g == "WI":
+            self._clear(stream)
         self.launch(cell_code(g, o, b), form, stream)
         self.back.enqueue(stream)
         self.torch.cuda.synchronize()

@@ -96,24 +96,39 @@ def test_every_cell_and_form_stores_every_item(gs, data, item, wg, n):
     r.close()
 
 
-@pytest.mark.parametrize("n", [100, 8192, 70000])
-def test_large_runs_clear_their_results_first(gs, data, n):
-    """Runs whose launch is long clear the results before it (a short one's
-    time would show it)."""
+@pytest.mark.parametrize("n,cell,form,cleared", [
+    (100, ("WI", "strong", "block"), "plain", False),
+    (65536, ("WI", "strong", "block"), "plain", False),
+    (70000, ("WI", "strong", "block"), "plain", True),
+    (70000, ("WG", "strong", "block"), "plain", False),
+    (70000, ("WI", "strong", "block"), "persistent", False),
+    (70000, ("WI", "strong", "block"), "graph", False)])
+def test_large_runs_clear_their_results_first(gs, data, n, cell, form, cleared):
+    """Launches of more work-item calls than a ring has slots clear the results
+    before it, on its stream; others would only be slower for it."""
     g, ctx = gs
     from conftest import POISON
     from paper_1705_06965_amd.fnv import FnvRunner
     import torch
+    code = {"plain": g.PLAIN, "persistent": g.PERSISTENT, "graph": g.GRAPH}[form]
     r = FnvRunner(ctx, data, np.arange(n, dtype=np.uint64), 64, wg_size=64)
     want = oracle.pread_fnv(data, np.arange(n, dtype=np.uint64), 64)
     side = torch.cuda.Stream()
     for s in (None, side):  # on the stream of the launch, so never after it
-        print("cleared", n, s, flush=True)
-        f, ret = r.run(stream=s)
+        print("cleared", n, cell, form, s, flush=True)
+        f, ret = r.run(*cell, form=code, stream=s)
         assert (f == want[0]).all() and (ret == want[1]).all()
+    switched = []
+    stream = torch.cuda.stream
     r.launch = lambda *a, **k: 0
     for s in (None, side):
-        f, ret = r.run(stream=s)
-        left = -12345 if n >= 8192 else POISON
+        torch.cuda.stream = lambda x: switched.append(x) or stream(x)
+        try:
+            f, ret = r.run(*cell, form=code, stream=s)
+        finally:
+            torch.cuda.stream = stream
+        left = -12345 if cleared else POISON
         assert (ret == left).all() and (f.view(np.int64) == left).all()
+        # torch's own stream is not switched to: that takes longer than the rest
+        assert len(switched) == (cleared and s is side)
     r.close()
