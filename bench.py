@@ -104,14 +104,17 @@ def parse():
 COMMON_SOURCES = ["include/gsys_device.hpp", "include/gsys_abi.h"]
 PROFILES = {
     "sweep": ("profiles/fnv4k_persistent_pread_sweep_1g.md",
-              ["paper_1705_06965_amd/csrc/k_fnv.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp"]),
+              ["paper_1705_06965_amd/csrc/k_fnv.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp",
+               "paper_1705_06965_amd/csrc/fnv_rules.hpp"]),
     "wordscan": ("profiles/wordscan_persistent_corpus_2000.md",
                  ["paper_1705_06965_amd/csrc/k_wordscan.hip"]),
     "permute": ("profiles/permute_pwrite_64m.md", ["paper_1705_06965_amd/csrc/k_permute.hip"]),
     "tiny": ("profiles/fnv4k_plain_tiny_64.md",
-             ["paper_1705_06965_amd/csrc/k_fnv.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp"]),
+             ["paper_1705_06965_amd/csrc/k_fnv.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp",
+              "paper_1705_06965_amd/csrc/fnv_rules.hpp"]),
     "serve": ("profiles/serve_persistent_mix_20k.md",
               ["paper_1705_06965_amd/csrc/k_serve.hip", "paper_1705_06965_amd/csrc/fnv_wave.hpp",
+               "paper_1705_06965_amd/csrc/fnv_rules.hpp",
                "paper_1705_06965_amd/csrc/host_copy.hpp"]),
     "kv": ("profiles/kv_serve_get_4m.md", ["paper_1705_06965_amd/csrc/k_kv.hip"]),
 }

@@ -88,8 +88,8 @@ inline bool many_lanes(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t bl
 // 300 of 64 KiB 452 against 567, 20 of 1 MiB 0.75 against 1.36 ms.  Not with
 // more calls than the ring has slots: those that wait for one poll host
 // memory, and from more compute units they slow the host more: 100,000 calls
-// of 576 bytes in work-groups of 1,024 (98 of them, a ring of 65,536) 11.0 ms,
-// spread 13.1.
+// of 576 bytes in work-groups of 1,024 (98 of them, a ring of 65,536) 10.8 ms,
+// spread 12.4.
 constexpr uint32_t spread_group(uint64_t n, uint32_t item_bytes, uint32_t wg, uint32_t cus,
                                 uint64_t slots) {
   if (item_bytes <= kParMinItem || n > slots) return wg;
